@@ -13,11 +13,11 @@ Prints one JSON line.  `value` is the bus bandwidth (S / t * 2(N-1)/N, in
 GB/s = 1e9 B/s, S = bytes per rank); `cpu_baseline` times the plain-C CPU
 oracle on the host on the same workload.  `roofline` prices the kernel
 against MI355X's 8 TB/s HBM peak on two bases:
-  * achieved / frac: the ring's algorithmic bytes, every rank-buffer, peer
-    and FIFO access the ring formulation issues (34 S for the peer-direct
-    Simple ring at 8 ranks fp32).  Its FIFO and forwarding traffic is partly
-    served by the 256 MB last-level cache, so this is memory-side traffic,
-    not HBM traffic alone (it exceeds what a pure HBM stream reaches here);
+  * achieved / frac: the bytes the algorithm moves through memory.  The ring
+    with its links in LDS and the direct algorithm move 2 N S.  With
+    --fifo-only every FIFO access of the ring counts too (44 S for Simple at
+    8 ranks fp32); FIFO traffic is partly served by the 256 MB last-level
+    cache, so that is memory-side traffic, not HBM traffic alone;
   * achieved_compulsory / frac_compulsory: 2 N S, each input read once and
     each output written once, the HBM lower bound of any AllReduce of N
     buffers in one memory: the HBM figure.
@@ -50,21 +50,33 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 PROFILES = os.path.join(ROOT, "profiles")
-KERNEL_SRC = os.path.join(ROOT, "paper_2603_11438_amd", "csrc", "ar_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_2603_11438_amd", "csrc")
+KERNEL_SRCS = ("ar_device.h", "ar_kernels.hip", "ring_lds.hip")
 
 
 def kernel_source_hash() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in KERNEL_SRCS:
+        with open(os.path.join(CSRC, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
+
+
+def links(info: dict) -> str | None:
+    """Where a ring plan's links are (plans here have no debug flags)."""
+    if info["algo_name"] != "ring":
+        return None
+    return "lds" if info["peer_direct"] else "fifo"
 
 
 def geometry_key(info: dict) -> str:
     """The launch geometry a counter summary was taken with."""
     if info["algo_name"] == "direct":
         return f"direct parts={info['nchannels']} W={info['nwaves']}"
+    if links(info) == "lds":
+        return f"ring links=lds C={info['nchannels']}"
     return (f"ring proto={info['proto_name']} C={info['nchannels']} W={info['nwaves']} "
-            f"chunk_elems={info['chunk_elems']} depth={info['fifo_depth']} "
-            f"peer={'direct' if info['peer_direct'] else 'fifo'}")
+            f"chunk_elems={info['chunk_elems']} depth={info['fifo_depth']} links=fifo")
 
 
 def read_traffic(workload: str, kernel: str, geometry: str) -> dict | None:
@@ -234,25 +246,23 @@ def main(argv=None) -> int:
     def roofline_of(info, ms, copy_gbs=None):
         t = ms / 1e3
         algo = info["algo_name"]
-        kernel = f"ring_{info['proto_name']}" if algo == "ring" else "direct"
-        if algo == "ring" and not info["peer_direct"] and info["proto_name"] == "simple":
-            kernel = "ring_simple_fifo"
+        fifo = links(info) == "fifo"
+        kernel = "direct" if algo != "ring" else f"ring_{info['proto_name']}_fifo" if fifo else "ring_lds"
         b_comp = ar.compulsory_bytes(s_bytes, n)
-        b_alg = (ar.ring_bytes(s_bytes, n, dtype, info["proto_name"], peer_direct=bool(info["peer_direct"]))
-                 if algo == "ring" else b_comp)
+        b_alg = ar.ring_bytes(s_bytes, n, dtype, info["proto_name"]) if fifo else b_comp
         achieved = b_alg / t / 1e9
         comp = b_comp / t / 1e9
         traffic = read_traffic(wl.name, kernel, geometry_key(info))
         roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": round(traffic["bytes"]) if traffic else None,
-                "kernel": (f"ring_kernel<{info['proto_name']}, {dtype}>" if algo == "ring"
-                           else f"direct_kernel<{dtype}>"),
+                "kernel": (f"direct_kernel<{dtype}>" if algo != "ring" else
+                           f"ring_kernel<{info['proto_name']}, {dtype}>" if fifo else f"lds_ring_kernel<{dtype}>"),
                 "algorithmic_bytes_per_launch": b_alg,
-                "basis": (f"{b_alg / s_bytes:.2f} S algorithmic bytes of the "
-                          + ("ring: rank buffers, peer reads and FIFOs; memory-side traffic, partly served by "
-                             "the last-level cache, not HBM alone" if algo == "ring" else
-                             "direct algorithm: each input read once, each output written once")),
+                "basis": (f"{b_alg / s_bytes:.2f} S algorithmic bytes: "
+                          + ("rank buffers and FIFOs; memory-side traffic, partly served by the last-level "
+                             "cache, not HBM alone" if fifo else
+                             "each input read once, each output written once")),
                 "geometry": geometry_key(info),
                 "achieved_compulsory": round(comp, 1),
                 "frac_compulsory": round(comp / HBM_PEAK_GBS, 4),
@@ -355,7 +365,7 @@ def main(argv=None) -> int:
                    "algo": info["algo_name"], "proto": info["proto_name"], "nchannels": info["nchannels"],
                    "chunk_bytes": info["chunk_elems"] * (4 if dtype == "f32" else 2),
                    "nwaves": info["nwaves"], "fifo_depth": info["fifo_depth"], "placement": info["placement"],
-                   "peer_access": ("direct" if info["peer_direct"] else "fifo") if info["algo_name"] == "ring" else None,
+                   "links": links(info),
                    "in_place": bool(args.in_place),
                    "parallelism": "simulated ring, 1 GPU"},
         "algbw_gbs": round(algbw, 2),

@@ -10,9 +10,12 @@
  * the policy programming model; section 5.3, Table 2 and Figure 2, where a
  * message-size-aware choice of ring protocol and channels beats the default).
  *
- * How.  A ring reduce-scatter followed by a ring all-gather.  Each simulated
- * rank is one group of workgroups; consecutive ranks exchange chunks through
- * FIFOs in device memory, with flags as the "link".  Segment-major layout:
+ * How.  A ring reduce-scatter followed by a ring all-gather.  Consecutive
+ * ranks exchange messages over a link.  By default a whole ring is one
+ * workgroup, a rank one of its waves, and the links are slots in the
+ * workgroup's LDS.  On request (AR_PLAN_FIFO_ONLY; also plans with debug
+ * flags) a rank is a group of workgroups and a link is a FIFO in device
+ * memory under one of three protocols.  Segment-major layout:
  * with A = 16 / element bytes, seg = roundup(ceil(count / N), A); segment s
  * covers elements [s*seg, min((s+1)*seg, count)) and is summed along the
  * ring starting at rank s (acc = x_s, then + x_{s+1}, ... + x_{s+N-1}), each
@@ -30,10 +33,13 @@
  * Nothing here is thread-safe for one plan: use a plan from one host thread
  * and keep at most one run of a plan in flight -- not on two streams at
  * once, not in two graph replays at once, not in a replay and an eager run
- * at once (its FIFOs and flag epochs are shared by all its runs; overlapping
- * runs corrupt each other's results or end in the watchdog).
+ * at once (a plan with links in memory shares its FIFOs and flag epochs
+ * between all its runs; overlapping runs corrupt each other's results or end
+ * in the watchdog).
  *
- * Ring launches on one device are ordered across streams.  A ring kernel's
+ * Launches of rings with links in memory are ordered across the streams of a
+ * device ("ring launch" in the rest of this paragraph; rings with links in
+ * LDS wait for no other workgroup and are not ordered).  Such a ring kernel's
  * workgroups wait on each other, so its grid needs the whole grid resident;
  * two ring grids dispatched side by side could each hold part of the device
  * while waiting for room the other occupies.  While all ring launches of a
@@ -67,7 +73,10 @@ extern "C" {
 /* Element types. */
 enum { AR_FLOAT32 = 0, AR_BFLOAT16 = 1 };
 
-/* Protocols (paper, section 2: the tuner chooses among LL, LL128, Simple).
+/* Protocols (paper, section 2: the tuner chooses among LL, LL128, Simple):
+ * how the receiver of a link in memory tells new data from old.  Links in
+ * LDS need none of this (a workgroup barrier publishes a step's messages);
+ * there a plan's protocol only decides which table geometry it gets.
  *   LL     8-byte lines: 4 bytes of data + 4-byte flag in one word; the
  *          reader checks the flag in the same load that brings the data
  *          (an aligned 8-byte access is single-copy atomic).
@@ -199,17 +208,22 @@ typedef struct ar_plan_desc {
  *                    run's sample is harvested without blocking by a later
  *                    ar_run, or by ar_plan_status; a run whose predecessor's
  *                    events are still pending is not timed.
- *   AR_PLAN_FIFO_ONLY  ring plans: carry every hop through the FIFOs.  By
- *                    default (the peer-direct mode) the second rank of each
- *                    reduce-scatter chain reads the chain start's input
- *                    from that rank's buffer (one hop and its flag fewer),
- *                    and the Simple ring also writes each finished
- *                    all-gather chunk straight into the next rank's output
- *                    buffer and forwards it from there (nothing moves on
- *                    the last hop); the LL and LL128 all-gathers keep their
- *                    lines, whose flags cannot live in a user buffer.  The
- *                    result bits are the same either way.  The direct
- *                    algorithm has no FIFOs and ignores the flag.
+ *   AR_PLAN_FIFO_ONLY  ring plans: links in memory, every hop through the
+ *                    FIFOs.  By default the links are in LDS: the plan's
+ *                    nchannels * nranks workgroups are that many rings, and
+ *                    chunk_bytes, fifo_depth, nwaves, placement and the
+ *                    watchdog do not apply.  A plan with debug flags and
+ *                    without this one has links in memory in the peer-direct
+ *                    mode: the second rank of each reduce-scatter chain
+ *                    reads the chain start's input from that rank's buffer
+ *                    (one hop and its flag fewer), and the Simple ring also
+ *                    writes each finished all-gather chunk straight into
+ *                    the next rank's output buffer and forwards it from
+ *                    there (nothing moves on the last hop); the LL and
+ *                    LL128 all-gathers keep their lines, whose flags cannot
+ *                    live in a user buffer.  The result bits are the same
+ *                    whichever way.  The direct algorithm has no links and
+ *                    ignores the flag.
  *   AR_PLAN_LL128_ORDERED  LL128 only: a reader uses a batch of lines only
  *                    from loads issued after it has seen every flag of the
  *                    batch current (it polls the 8-byte flags, then reads
@@ -219,7 +233,10 @@ typedef struct ar_plan_desc {
  *                    trip per batch.  Other protocols ignore the flag. */
 enum { AR_PLAN_PROFILE = 1u, AR_PLAN_FIFO_ONLY = 2u, AR_PLAN_LL128_ORDERED = 4u };
 
-/* Resolved plan geometry (after the tuner and defaults). */
+/* Resolved plan geometry (after the tuner and defaults).  The fields of
+ * links in memory (waves, chunk, slots, FIFO and flag bytes, messages, wire
+ * bytes) are filled for every ring plan, also for one whose links are in LDS,
+ * which uses and allocates none of it. */
 typedef struct ar_plan_info {
     int nranks, dtype, proto, nchannels, nwaves, fifo_depth, placement;
     int grid;              /* workgroups = nchannels * nranks */
@@ -244,10 +261,9 @@ typedef struct ar_plan_info {
                               chunks written into the next rank's output */
     int algo;              /* AR_ALGO_RING or AR_ALGO_DIRECT */
     int coll;              /* AR_COLL_* */
-    int peer_direct;       /* 1: the ring reads the chain start's input
-                              directly, and the Simple ring writes all-gather
-                              chunks into the next rank's output (see
-                              AR_PLAN_FIFO_ONLY) */
+    int peer_direct;       /* 1: links in LDS, or with debug flags the
+                              peer-direct mode in memory; 0: every hop through
+                              the FIFOs (see AR_PLAN_FIFO_ONLY) */
     int direct_unroll;     /* direct algorithm: units per thread and iteration */
 } ar_plan_info;
 
@@ -256,8 +272,8 @@ typedef struct ar_plan_info {
 /* Create a plan for AllReduce of `count` elements of `dtype` over `nranks`
  * simulated ranks on the current HIP device.  proto = AR_PROTO_AUTO or
  * nchannels = 0 consults the active tuner with msg_bytes = count * element
- * size.  The plan owns its FIFO, flag and status memory (device memory on
- * the current device, zeroed here, freed by ar_destroy).  Returns NULL on
+ * size.  A plan with links in memory owns its FIFO, flag and status memory
+ * (device memory on the current device, zeroed here, freed by ar_destroy).  Returns NULL on
  * error (see ar_last_error): AR_ERR_ARG for out-of-range arguments,
  * AR_ERR_OCCUPANCY if nchannels * nranks workgroups cannot be co-resident,
  * AR_ERR_NOMEM / AR_ERR_HIP for allocation or device failures. */
@@ -296,7 +312,8 @@ int ar_run_oop(ar_plan_t *plan, const void *const *send, void *const *recv, void
  * forbid hipMalloc.  It runs the collective `desc` describes (as ar_plan_ex
  * would plan it: the tuner, defaults and clamps are the same) from send[r]
  * to recv[r] on `stream`, with the same numerics and buffer rules as
- * ar_run_oop, and calls no hipMalloc, hipFree, event or stream creation:
+ * ar_run_oop, and calls no hipMalloc, hipFree, event or stream creation.
+ * Links in LDS use no device memory; for links in memory
  * the ring's FIFOs, flags and control words live in a static device array
  * of AR_NOALLOC_SCRATCH_BYTES per device, which every call on that device
  * shares and which keeps the last call's contents until the process ends.
@@ -305,7 +322,8 @@ int ar_run_oop(ar_plan_t *plan, const void *const *send, void *const *recv, void
  * on one device race on the array: keep them on one stream, or order them.
  * Ring launches made here are not ordered against other streams' ring
  * launches (see the conventions above); the caller orders them.
- * Errors: AR_ERR_SCRATCH when the ring's FIFO, flags and control words need
+ * Errors: AR_ERR_SCRATCH when the ring's FIFO, flags and control words as
+ * ar_plan_info gives them (wherever its links are) come to
  * more than AR_NOALLOC_SCRATCH_BYTES (pick smaller chunks, fewer channels or
  * waves, or the direct algorithm, which needs no scratch); AR_ERR_UNSUPPORTED
  * for AR_PLAN_PROFILE (it needs events); otherwise as ar_plan_ex and
@@ -367,7 +385,8 @@ void ar_destroy(ar_plan_t *plan);
 /* Resolved geometry of an existing plan. */
 int ar_plan_get_info(const ar_plan_t *plan, ar_plan_info *out);
 
-/* Device memory the plan holds (FIFO + flags + control words), bytes. */
+/* Device memory the plan holds (FIFO + flags + control words), bytes; 0 for
+ * the direct algorithm and for links in LDS. */
 size_t ar_plan_workspace_bytes(const ar_plan_t *plan);
 
 /* Resolve a description to its geometry on the host alone (tuner, defaults,

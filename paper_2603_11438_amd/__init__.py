@@ -577,7 +577,8 @@ def alg_bandwidth(msg_bytes: int, seconds: float) -> float:
 
 
 def ring_bytes(msg_bytes: int, nranks: int, dtype="f32", proto="simple", peer_direct: bool = False) -> float:
-    """Bytes the ring formulation moves through global memory per AllReduce.
+    """Bytes the ring with its links in memory moves through global memory
+    per AllReduce.  (With its links in LDS it moves compulsory_bytes.)
 
     Through FIFOs: every rank reads its input and writes its output (2 N S),
     and every element crosses 2(N-1) links, each written to a FIFO once and

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import shutil
 import subprocess
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -12,12 +13,12 @@ INCLUDE = os.path.join(ROOT, "include")
 LIBDIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(LIBDIR, "libar.so")
 
-SOURCES = ["ar_kernels.hip", "ar_runtime.cpp", "ar_tuner.cpp", "ar_profile.cpp", "ar_noalloc.hip"]
+SOURCES = ["ar_kernels.hip", "ring_lds.hip", "ar_runtime.cpp", "ar_tuner.cpp", "ar_profile.cpp", "ar_noalloc.hip"]
 
 # -packed-fp32-ops: no packed fp32 instructions in device code.
 # -ffp-contract=off / no fast-math: every fp32 add is one IEEE RNE operation.
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-ffp-contract=off", "-fno-fast-math", "-Wall", "-Wno-unused-variable",
     "-Wno-unused-but-set-variable",
@@ -35,15 +36,23 @@ def build(verbose: bool = False) -> str:
     """Compile every HIP/C++ source of libar into _lib/libar.so (always rebuilds)."""
     os.makedirs(LIBDIR, exist_ok=True)
     tmp = LIB + ".tmp"
-    cmd = [hipcc(), *HIPCC_FLAGS, "-I", INCLUDE, "-I", CSRC,
-           *[os.path.join(CSRC, s) for s in SOURCES], "-o", tmp]
-    env = dict(os.environ)
-    r = subprocess.run(cmd, cwd=PKG, env=env, capture_output=True, text=True)
-    out = (r.stdout or "") + (r.stderr or "")
+    with tempfile.TemporaryDirectory() as objdir:
+        # One compiler per source, at the same time; then one link.
+        jobs = []
+        for s in SOURCES:
+            obj = os.path.join(objdir, s + ".o")
+            cmd = [hipcc(), *HIPCC_FLAGS, "-c", "-I", INCLUDE, "-I", CSRC, os.path.join(CSRC, s), "-o", obj]
+            jobs.append((obj, subprocess.Popen(cmd, cwd=PKG, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                                               text=True)))
+        done = [(obj, job.communicate()[0], job.returncode) for obj, job in jobs]
+        if not any(rc for _, _, rc in done):
+            r = subprocess.run([hipcc(), "--offload-arch=gfx950", "-shared", *[obj for obj, _, _ in done], "-o", tmp],
+                               cwd=PKG, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+            done.append((tmp, r.stdout, r.returncode))
     # hipcc's host pass does not know the packed-fp32 target feature; that
     # warning is expected and harmless.
-    lines = [l for l in out.splitlines() if "packed-fp32-ops" not in l]
-    if r.returncode != 0:
+    lines = [l for _, out, _ in done for l in (out or "").splitlines() if "packed-fp32-ops" not in l]
+    if any(rc for _, _, rc in done):
         raise RuntimeError("libar build failed:\n" + "\n".join(lines))
     if verbose and lines:
         print("\n".join(lines))

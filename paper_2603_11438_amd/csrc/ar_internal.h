@@ -68,7 +68,8 @@ int default_nwaves(int proto);
 int default_depth(int proto);
 size_t default_chunk_bytes(int proto);
 
-// Kernel launchers (ar_kernels.hip).
+// Kernel launchers (ar_kernels.hip; launch_ring_lds: ring_lds.hip).
+int launch_ring_lds(const ar_plan_info &info, const RingArgs &args, void *stream);
 int launch_ring(const ar_plan_info &info, const RingArgs &args, void *stream);
 int launch_fill_u32(uint32_t *p, size_t n, uint32_t value, void *stream);
 int launch_copy(const void *src, void *dst, size_t bytes, void *stream);
@@ -76,6 +77,14 @@ int ring_occupancy(int proto, int dtype, int block, int *blocks_per_cu);
 int launch_bf16_round(const float *in, uint16_t *out, size_t n, void *stream);
 
 // Run-time helpers of ar_runtime.cpp.
+// Where a ring plan's links are.  In LDS, unless the plan asks for links in
+// memory: FIFO-only plans, and plans with debug flags, whose hooks (skipped
+// posts, jitter, the line checker, the step trace) belong to lines and
+// counters in memory.
+inline bool links_in_lds(const ar_plan_info &g, const ar_plan_desc &d)
+{
+    return g.algo == AR_ALGO_RING && g.peer_direct && d.debug_flags == 0;
+}
 constexpr uint32_t kDefaultTimeoutUs = 2000000;  // 2 s per flag wait
 constexpr uint64_t kTicksPerUs = 100;            // 100 MHz real-time counter
 // Bytes of each rank's send and recv buffer for a collective's geometry.

@@ -1,7 +1,9 @@
-// Ring AllReduce kernels for gfx950 (MI355X): reduce-scatter then
-// all-gather around a ring of N simulated ranks whose buffers all live in
-// one GPU's memory, under one of three protocols (LL, LL128, Simple); the
-// same ring runs ReduceScatter and AllGather alone.  Also here: the direct
+// Ring AllReduce kernels for gfx950 (MI355X) with their links in memory:
+// reduce-scatter then all-gather around a ring of N simulated ranks whose
+// buffers all live in one GPU's memory, under one of three protocols (LL,
+// LL128, Simple); the same ring runs ReduceScatter and AllGather alone.
+// FIFO-only plans and plans with debug flags run these; every other ring has
+// its links in LDS (ring_lds.hip).  Also here: the direct
 // (two-shot) algorithm, which reads every rank's segment and writes the sum
 // to every rank with no FIFOs, and the streaming copy of the one-rank case.
 //
@@ -45,30 +47,10 @@
 // wave that times out raises the plan's abort word and status bit, and all
 // waves leave their loops when they see the abort word, so the kernel always
 // drains.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
-#include "ar_internal.h"
+#include "ar_device.h"
 
 namespace ar {
 namespace dev {
-
-typedef uint32_t u32x4 __attribute__((__vector_size__(16)));
-typedef uint32_t u32x2 __attribute__((__vector_size__(8)));
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-
-// Cache-policy operand of gfx950 buffer instructions.
-enum : int { kPolPlain = 0, kPolSc0 = 1, kPolNt = 2, kPolSc1 = 16 };
-// The policies are fixed, not build options.  A FIFO line (or, in the
-// peer-direct mode, an output element) is written on one XCD and read on
-// another, behind a different L2; without the device-scope bit on both the
-// write and the read, a reader can be served a stale copy and the ring
-// returns wrong sums or waits until the watchdog fires.
-constexpr int kFifoLd = kPolSc1;  // device-coherent FIFO reads
-constexpr int kFifoSt = kPolSc1;  // device-coherent FIFO writes
-constexpr int kInPol = kPolNt;    // rank inputs: read once, streamed
-constexpr int kOutPol = kPolNt;   // rank outputs: written once, streamed
-static_assert((kFifoLd & kPolSc1) != 0 && (kFifoSt & kPolSc1) != 0, "FIFO accesses must be device-coherent");
 
 enum Kind : int {
     kSend = 0,            // own input -> wire (reduce-scatter start)
@@ -101,115 +83,6 @@ struct KindTraits {
     static constexpr bool kWriteOut = kReduceToY || kRecvAG || KIND == kCopySend;
     static constexpr bool kCopyInToY = KIND == kCopySend;                                      // y = own input
 };
-
-template <int DT> struct Elem;
-template <> struct Elem<AR_FLOAT32> { static constexpr uint32_t E = 4, A = 4; };
-template <> struct Elem<AR_BFLOAT16> { static constexpr uint32_t E = 2, A = 8; };
-
-__device__ __forceinline__ Rsrc make_rsrc(const void *p, uint64_t bytes)
-{
-    // Word 3 = 0x00020000: raw 32-bit dword format, as on the rest of CDNA.
-    uint32_t n = bytes > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)n, 0x00020000);
-}
-
-template <int POL> __device__ __forceinline__ u32x4 ld128(Rsrc r, uint32_t off)
-{
-    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, POL);
-}
-template <int POL> __device__ __forceinline__ u32x2 ld64(Rsrc r, uint32_t off)
-{
-    return __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, POL);
-}
-template <int POL> __device__ __forceinline__ uint32_t ld32(Rsrc r, uint32_t off)
-{
-    return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, POL);
-}
-template <int POL> __device__ __forceinline__ uint32_t ld16(Rsrc r, uint32_t off)
-{
-    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, POL);
-}
-template <int POL> __device__ __forceinline__ void st128(Rsrc r, uint32_t off, u32x4 v)
-{
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, POL);
-}
-template <int POL> __device__ __forceinline__ void st64(Rsrc r, uint32_t off, u32x2 v)
-{
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, POL);
-}
-template <int POL> __device__ __forceinline__ void st32(Rsrc r, uint32_t off, uint32_t v)
-{
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, POL);
-}
-template <int POL> __device__ __forceinline__ void st16(Rsrc r, uint32_t off, uint32_t v)
-{
-    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)v, r, (int)off, 0, POL);
-}
-
-// A buffer offset outside every resource built by the ring steps (each covers
-// at most one step's data or one FIFO slot, far below 2^31 bytes): a load
-// there returns zeros and a store there is dropped, by the hardware's range
-// check.  Lanes past the end of a message use it instead of a branch, which
-// keeps a batch of accesses straight-line code; the compiler can then wait
-// for exactly the loads an instruction needs instead of for every
-// outstanding access (a branch around each access makes it wait for all of
-// them, earlier stores included, before each store).
-constexpr uint32_t kOobOff = 0x80000000u;
-__device__ __forceinline__ uint32_t in_range(bool ok, uint32_t off) { return ok ? off : kOobOff; }
-
-__device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
-
-// True on every lane when p holds on any active lane; the result is a
-// wave-uniform value the compiler knows to be uniform.
-//
-// Uniformity matters throughout the ring steps: a branch on the lane (such as
-// "lane 0 stores the flag") whose join merges any value makes the compiler
-// treat everything that depends on it as per-lane.  The step loop then runs
-// under an execution mask, loop-carried counters and pointers move into
-// vector registers, and every buffer access is wrapped in a loop that reads
-// its descriptor lane by lane.  So flags are stored by every lane (the same
-// value to the same address: one write), and partial units and groups use
-// out-of-range offsets instead of lane branches.
-__device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
-
-// The lane index as a value the compiler may not hoist out of the step loop:
-// a step's per-lane offsets are then recomputed each step (a few ALU ops)
-// instead of being held in registers across every step of the kernel.
-__device__ __forceinline__ uint32_t step_lane()
-{
-    uint32_t l = lane_id();
-    asm volatile("" : "+v"(l));
-    return l;
-}
-
-__device__ __forceinline__ uint64_t uniform64(uint64_t v)
-{
-    uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// ---- fp32 / bf16 ------------------------------------------------------------
-
-__device__ __forceinline__ float as_f32(uint32_t u) { return __builtin_bit_cast(float, u); }
-__device__ __forceinline__ uint32_t as_u32(float f) { return __builtin_bit_cast(uint32_t, f); }
-
-// bf16 -> fp32 is exact: the bf16 bits are the top half of the fp32 word.
-__device__ __forceinline__ float bf16_lo(uint32_t w) { return as_f32(w << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t w) { return as_f32(w & 0xFFFF0000u); }
-
-// fp32 -> bf16, round to nearest even; NaN -> quiet NaN 0x7FC0.
-__device__ __forceinline__ uint32_t bf16_rne(float f)
-{
-    uint32_t u = as_u32(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
-{
-    return bf16_rne(lo) | (bf16_rne(hi) << 16);
-}
 
 // ---- flags, fences, watchdog ----------------------------------------------
 
@@ -1942,34 +1815,35 @@ __global__ void bf16_round_kernel(const float *in, uint16_t *out, size_t n)
 typedef void (*RingFn)(RingArgs);
 
 // dag: the peer-direct mode (chains start with a peer read; the Simple
-// ring also writes its all-gather into the next rank's output).
+// ring also writes its all-gather into the next rank's output).  Here only
+// plans with debug flags run it: without them its links are in LDS.
 template <int DT, bool DBG, bool ORD, bool DAG>
 __host__ RingFn ll128_fn(bool wide)
 {
     return wide ? ring_kernel<AR_PROTO_LL128, DT, DAG, DBG, 4, ORD> : ring_kernel<AR_PROTO_LL128, DT, DAG, DBG, 2, ORD>;
 }
 
-template <int DT, bool DBG>
-__host__ RingFn ring_fn_of(int proto, bool dag, bool wide, bool ordered)
+template <int DT, bool DBG, bool DAG>
+__host__ RingFn ring_fn_of(int proto, bool wide, bool ordered)
 {
-    if (proto == AR_PROTO_LL)
-        return dag ? ring_kernel<AR_PROTO_LL, DT, true, DBG, 2, false> : ring_kernel<AR_PROTO_LL, DT, false, DBG, 2, false>;
-    if (proto == AR_PROTO_LL128) {
-        if (dag) return ordered ? ll128_fn<DT, DBG, true, true>(wide) : ll128_fn<DT, DBG, false, true>(wide);
-        return ordered ? ll128_fn<DT, DBG, true, false>(wide) : ll128_fn<DT, DBG, false, false>(wide);
-    }
-    return dag ? ring_kernel<AR_PROTO_SIMPLE, DT, true, DBG, 2, false> : ring_kernel<AR_PROTO_SIMPLE, DT, false, DBG, 2, false>;
+    if (proto == AR_PROTO_LL) return ring_kernel<AR_PROTO_LL, DT, DAG, DBG, 2, false>;
+    if (proto == AR_PROTO_LL128) return ordered ? ll128_fn<DT, DBG, true, DAG>(wide) : ll128_fn<DT, DBG, false, DAG>(wide);
+    return ring_kernel<AR_PROTO_SIMPLE, DT, DAG, DBG, 2, false>;
 }
 
 // dbg: a plan with debug flags runs the instance with the debug hooks.
 // wide: LL128 with four-access batches; ordered: AR_PLAN_LL128_ORDERED.
+template <int DT>
+__host__ RingFn ring_fn_dt(int proto, bool dag, bool dbg, bool wide, bool ordered)
+{
+    if (!dbg) return dag ? nullptr : ring_fn_of<DT, false, false>(proto, wide, ordered);
+    return dag ? ring_fn_of<DT, true, true>(proto, wide, ordered) : ring_fn_of<DT, true, false>(proto, wide, ordered);
+}
+
 __host__ RingFn ring_fn(int proto, int dtype, bool dag, bool dbg, bool wide, bool ordered)
 {
-    if (dtype == AR_FLOAT32)
-        return dbg ? ring_fn_of<AR_FLOAT32, true>(proto, dag, wide, ordered)
-                   : ring_fn_of<AR_FLOAT32, false>(proto, dag, wide, ordered);
-    return dbg ? ring_fn_of<AR_BFLOAT16, true>(proto, dag, wide, ordered)
-               : ring_fn_of<AR_BFLOAT16, false>(proto, dag, wide, ordered);
+    return dtype == AR_FLOAT32 ? ring_fn_dt<AR_FLOAT32>(proto, dag, dbg, wide, ordered)
+                               : ring_fn_dt<AR_BFLOAT16>(proto, dag, dbg, wide, ordered);
 }
 
 // LL128 takes four-access batches when one wave's message spans more than
@@ -2001,6 +1875,7 @@ int launch_ring(const ar_plan_info &info, const RingArgs &args, void *stream)
                                                  : dev::ring_fn(info.proto, info.dtype, info.peer_direct != 0,
                                                                 args.debug != 0, dev::ll128_wide(info),
                                                                 args.ll128_ordered != 0);
+    if (!fn) return AR_ERR_UNSUPPORTED;
     RingArgs a = args;
     void *kargs[] = {&a};
     hipError_t e = hipLaunchKernel((const void *)fn, dim3((unsigned)info.grid), dim3((unsigned)info.block), kargs,
@@ -2014,6 +1889,7 @@ int ring_occupancy(int proto, int dtype, int block, int *blocks_per_cu)
     int best = 1 << 30;
     for (int v = 0; v < 16; ++v) {
         dev::RingFn fn = dev::ring_fn(proto, dtype, (v & 1) != 0, (v & 2) != 0, (v & 4) != 0, (v & 8) != 0);
+        if (!fn) continue;
         int n = 0;
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)fn, block, 0);
         if (e != hipSuccess) return AR_ERR_HIP;

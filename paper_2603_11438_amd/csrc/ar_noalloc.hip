@@ -77,6 +77,11 @@ extern "C" int ar_run_noalloc(const ar_plan_desc *desc, const void *const *send,
     size_t flags_off = 0, fifo_off = 0;
     const size_t need = workspace_layout(g, &flags_off, &fifo_off);
     if (need > kScratchBytes) return ret(AR_ERR_SCRATCH);
+    if (links_in_lds(g, d)) {
+        // Links in LDS: no scratch, so nothing to clear.
+        fill_args(g, d, (uint64_t)tus * kTicksPerUs, send, recv, nullptr, nullptr, nullptr, &a);
+        return ret(launch_ring_lds(g, a, stream));
+    }
     void *base = nullptr;
     rc = scratch_of(dev, &base);
     if (rc != AR_OK) return ret(rc);

@@ -183,11 +183,13 @@ void fill_args(const ar_plan_info &g, const ar_plan_desc &d, uint64_t timeout_ti
 
 namespace {
 
-// Launch a ring or direct kernel.  A ring launch goes through the device's
-// gate, which keeps ring grids of different streams from overlapping.
-int launch_gated(int dev, const ar_plan_info &g, const RingArgs &a, void *stream)
+// Launch a ring or direct kernel.  A launch of a ring with links in memory
+// goes through the device's gate, which keeps such grids of different streams
+// from overlapping; the others wait for no workgroup.
+int launch_gated(int dev, const ar_plan_info &g, const ar_plan_desc &d, const RingArgs &a, void *stream)
 {
     if (g.algo != AR_ALGO_RING) return launch_ring(g, a, stream);
+    if (links_in_lds(g, d)) return launch_ring_lds(g, a, stream);
     RingGate<HipGateApi>::Ticket t;
     int rc = g_ring_gate.before(dev, (hipStream_t)stream, t);
     if (rc != 0) return AR_ERR_HIP;
@@ -310,7 +312,7 @@ int run_impl(ar_plan_t *p, const void *const *send, void *const *recv, void *str
         harvest_profile(p);
         if (!p->ev_pending && hipEventRecord(p->ev_start, (hipStream_t)stream) == hipSuccess) timed = true;
     }
-    rc = launch_gated(dev, g, a, stream);
+    rc = launch_gated(dev, g, p->desc, a, stream);
     if (rc != AR_OK) return ret(rc);
     if (timed && hipEventRecord(p->ev_stop, (hipStream_t)stream) == hipSuccess) p->ev_pending = true;
     return AR_OK;
@@ -343,7 +345,7 @@ ar_plan_t *ar_plan_ex(const ar_plan_desc *desc)
             return fail<ar_plan_t>(AR_ERR_HIP);
         }
     }
-    if (info.grid > 0 && info.algo == AR_ALGO_RING) {
+    if (info.grid > 0 && info.algo == AR_ALGO_RING && !links_in_lds(info, d)) {
         size_t flags_off = 0, fifo_off = 0;
         p->ws_bytes = workspace_layout(info, &flags_off, &fifo_off);
         if (hipMalloc((void **)&p->ws, p->ws_bytes) != hipSuccess) {

@@ -676,8 +676,8 @@ def configs(args):
                 info = plan.info
                 st = _stats(times)
                 t = st["p50_us"] * 1e-6
-                rb = ar.ring_bytes(size, n, dtype, info["proto_name"], peer_direct=bool(info["peer_direct"]))
                 cb = ar.compulsory_bytes(size, n)
+                rb = cb if info["peer_direct"] else ar.ring_bytes(size, n, dtype, info["proto_name"])  # links in LDS / FIFOs
                 rec = {"workload": name, "size": size, "dtype": dtype, **cfg, "proto": info["proto_name"],
                        "peer_direct": info["peer_direct"],
                        "nchannels_eff": info["nchannels"], "chunk_eff": info["chunk_elems"] * (4 if dtype == "f32" else 2),
