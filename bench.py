@@ -51,7 +51,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 PROFILES = os.path.join(ROOT, "profiles")
 CSRC = os.path.join(ROOT, "paper_2603_11438_amd", "csrc")
-KERNEL_SRCS = ("ar_device.h", "ar_kernels.hip", "ring_lds.hip")
+KERNEL_SRCS = ("ar_device.h", "ar_kernels.hip", "ring_lds.hip", "direct.hip")
 
 
 def kernel_source_hash() -> str:

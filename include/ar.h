@@ -199,7 +199,8 @@ typedef struct ar_plan_desc {
     int algo;              /* AR_ALGO_* */
     int coll;              /* AR_COLL_* (0 = AllReduce) */
     int direct_unroll;     /* direct algorithm: 1 or 2 units per thread and
-                              iteration; 0 asks the tuner / default */
+                              iteration (times 2 for 2..4 ranks, times 4 for
+                              AllGather); 0 asks the tuner / default */
 } ar_plan_desc;
 
 /* Plan flags.
@@ -425,7 +426,7 @@ typedef struct ar_tune_out {
     int direct_nwaves;     /* direct algorithm: waves per workgroup (0 = 4) */
     int direct_unroll;     /* direct algorithm: 16-byte units per thread and
                               iteration, 1 or 2 (0 = by size: 2 up to 8 MiB
-                              per rank, 1 above) */
+                              per rank, 1 above); see ar_plan_desc */
 } ar_tune_out;
 
 /* A tuner: fill *out from *ctx; return 0 on success.  A non-zero return, or

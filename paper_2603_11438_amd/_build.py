@@ -13,7 +13,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIBDIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(LIBDIR, "libar.so")
 
-SOURCES = ["ar_kernels.hip", "ring_lds.hip", "ar_runtime.cpp", "ar_tuner.cpp", "ar_profile.cpp", "ar_noalloc.hip"]
+SOURCES = ["ar_kernels.hip", "ring_lds.hip", "direct.hip", "ar_runtime.cpp", "ar_tuner.cpp", "ar_profile.cpp", "ar_noalloc.hip"]
 
 # -packed-fp32-ops: no packed fp32 instructions in device code.
 # -ffp-contract=off / no fast-math: every fp32 add is one IEEE RNE operation.

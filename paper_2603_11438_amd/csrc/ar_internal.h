@@ -68,7 +68,9 @@ int default_nwaves(int proto);
 int default_depth(int proto);
 size_t default_chunk_bytes(int proto);
 
-// Kernel launchers (ar_kernels.hip; launch_ring_lds: ring_lds.hip).
+// Kernel launchers (ar_kernels.hip; launch_ring_lds: ring_lds.hip,
+// launch_direct: direct.hip).
+int launch_direct(const ar_plan_info &info, const RingArgs &args, void *stream);
 int launch_ring_lds(const ar_plan_info &info, const RingArgs &args, void *stream);
 int launch_ring(const ar_plan_info &info, const RingArgs &args, void *stream);
 int launch_fill_u32(uint32_t *p, size_t n, uint32_t value, void *stream);

@@ -3,9 +3,8 @@
 // buffers all live in one GPU's memory, under one of three protocols (LL,
 // LL128, Simple); the same ring runs ReduceScatter and AllGather alone.
 // FIFO-only plans and plans with debug flags run these; every other ring has
-// its links in LDS (ring_lds.hip).  Also here: the direct
-// (two-shot) algorithm, which reads every rank's segment and writes the sum
-// to every rank with no FIFOs, and the streaming copy of the one-rank case.
+// its links in LDS (ring_lds.hip).  Also here: the streaming copy of the
+// one-rank case.
 //
 // Work decomposition.  Grid = nchannels * nranks workgroups; workgroup
 // (channel c, rank r) holds `nwaves` wavefronts and each wavefront is an
@@ -1601,172 +1600,6 @@ __global__ __launch_bounds__(1024) void ring_kernel(RingArgs a)
     }
 }
 
-// ===================================================================== direct
-//
-// Two-shot direct AllReduce: workgroup b works on segment s = b mod N (part
-// b / N of its parts); a thread loads one 16-byte unit of segment s from
-// every rank (ranks s, s+1, ..., s+N-1 in that order), sums them in that
-// chain order -- the same additions, in the same order, as the ring's
-// reduce-scatter -- and stores the result to every rank.  Every element is
-// read once per rank and written once per rank: the compulsory 2 N S bytes,
-// no FIFOs, no flags, no waits.  In place is safe: each element is read and
-// then written by the same thread.
-//
-// The same kernel runs the other collectives directly: ReduceScatter sums
-// block s along the chain that starts at rank s+1 (the ring's order for a
-// block that ends at rank s) and writes it to rank s only; AllGather copies
-// rank s's block to block s of every rank.
-
-template <int DT, int NMAX, int U>
-__global__ __launch_bounds__(1024) void direct_kernel(RingArgs a)
-{
-    constexpr uint32_t E = Elem<DT>::E;
-    constexpr uint32_t A = Elem<DT>::A;
-    const uint32_t N = a.nranks;
-    const uint32_t parts = a.nchannels;
-    const uint32_t s = blockIdx.x % N;
-    const uint32_t part = blockIdx.x / N;
-    const uint32_t coll = a.coll;
-    const uint32_t nsrc = coll == AR_COLL_ALLGATHER ? 1u : N;       // chain length
-    const uint32_t first = coll == AR_COLL_REDUCESCATTER ? s + 1 : s;  // chain start rank
-    const uint32_t nout = coll == AR_COLL_REDUCESCATTER ? 1u : N;    // ranks written
-    const uint64_t seg_lo = (uint64_t)s * a.seg;
-    if (seg_lo >= a.count) return;
-    const uint64_t seg_hi = seg_lo + a.seg < a.count ? seg_lo + a.seg : a.count;
-    const uint64_t len = seg_hi - seg_lo;
-    const uint64_t nfull_all = len / A;
-    const uint32_t rem = (uint32_t)(len % A);
-    const uint32_t tid = threadIdx.x, nth = blockDim.x;
-
-    // Rank j of the chain is rank (first + j) mod N.  AllGather reads a
-    // block-sized source, ReduceScatter writes a block-sized destination.
-    // A descriptor covers `bytes` from byte `off` of the segment: buffer
-    // offsets are 32-bit, so a segment is walked in windows of kWinUnits
-    // units (one window up to 1 GiB per segment).
-    auto in_rsrc = [&](uint32_t j, uint64_t off, uint64_t bytes) {
-        const uint32_t r = (first + j) % N;
-        return make_rsrc(a.src[r] + (coll == AR_COLL_ALLGATHER ? 0 : seg_lo * E) + off, bytes);
-    };
-    auto out_rsrc = [&](uint32_t i, uint64_t off, uint64_t bytes) {
-        const uint32_t r = coll == AR_COLL_REDUCESCATTER ? s : i;
-        return make_rsrc(a.dst[r] + (coll == AR_COLL_REDUCESCATTER ? 0 : seg_lo * E) + off, bytes);
-    };
-    constexpr uint64_t kWinUnits = 1ull << 26;
-
-    auto chain = [&](const u32x4 *v, float *acc) {
-        if (E == 4) {
-            for (int i = 0; i < 4; ++i) acc[i] = as_f32(v[0][i]);
-        } else {
-            for (int i = 0; i < 4; ++i) {
-                acc[2 * i] = bf16_lo(v[0][i]);
-                acc[2 * i + 1] = bf16_hi(v[0][i]);
-            }
-        }
-#pragma unroll
-        for (int j = 1; j < NMAX; ++j) {
-            if ((uint32_t)j < nsrc) {
-                if (E == 4) {
-                    for (int i = 0; i < 4; ++i) acc[i] = acc[i] + as_f32(v[j][i]);
-                } else {
-                    for (int i = 0; i < 4; ++i) {
-                        acc[2 * i] = acc[2 * i] + bf16_lo(v[j][i]);
-                        acc[2 * i + 1] = acc[2 * i + 1] + bf16_hi(v[j][i]);
-                    }
-                }
-            }
-        }
-    };
-    auto narrow = [&](const float *acc) {
-        u32x4 y;
-        if (E == 4) {
-            for (int i = 0; i < 4; ++i) y[i] = as_u32(acc[i]);
-        } else {
-            for (int i = 0; i < 4; ++i) y[i] = pack_bf16(acc[2 * i], acc[2 * i + 1]);
-        }
-        return y;
-    };
-
-    for (uint64_t w0 = 0; w0 < nfull_all; w0 += kWinUnits) {
-        const uint32_t nfull = (uint32_t)(nfull_all - w0 < kWinUnits ? nfull_all - w0 : kWinUnits);
-        const uint64_t woff = w0 * 16, wbytes = (uint64_t)nfull * 16;
-        for (uint32_t base = part * nth * U; base < nfull; base += parts * nth * U) {
-            u32x4 v[U][NMAX];
-#pragma unroll
-            for (int j = 0; j < NMAX; ++j) {
-                if ((uint32_t)j < nsrc) {
-                    const Rsrc rin = in_rsrc(j, woff, wbytes);
-#pragma unroll
-                    for (int t = 0; t < U; ++t) {
-                        const uint32_t u = base + t * nth + tid;
-                        v[t][j] = ld128<kInPol>(rin, in_range(u < nfull, u * 16));
-                    }
-                }
-            }
-            u32x4 y[U];
-#pragma unroll
-            for (int t = 0; t < U; ++t) {
-                if (coll == AR_COLL_ALLGATHER) {
-                    y[t] = v[t][0];  // a copy keeps every bit, NaN payloads included
-                } else {
-                    float acc[A];
-                    chain(v[t], acc);
-                    y[t] = narrow(acc);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < NMAX; ++r) {
-                if ((uint32_t)r < nout) {
-                    const Rsrc rout = out_rsrc(r, woff, wbytes);
-#pragma unroll
-                    for (int t = 0; t < U; ++t) {
-                        const uint32_t u = base + t * nth + tid;
-                        st128<kOutPol>(rout, in_range(u < nfull, u * 16), y[t]);
-                    }
-                }
-            }
-        }
-    }
-    if (rem && part == 0 && tid == 0) {
-        // Partial last unit of the buffer: element-wise loads and stores
-        // (every index below is a compile-time constant after unrolling).
-        u32x4 v[NMAX];
-#pragma unroll
-        for (int j = 0; j < NMAX; ++j) {
-            u32x4 x = {0, 0, 0, 0};
-            if ((uint32_t)j < nsrc) {
-                const Rsrc rin = in_rsrc(j, nfull_all * 16, (uint64_t)rem * E);
-#pragma unroll
-                for (int i = 0; i < (int)A; ++i) {
-                    if ((uint32_t)i < rem) {
-                        if (E == 4) x[i] = ld32<kInPol>(rin, 4 * i);
-                        else x[i >> 1] |= ld16<kInPol>(rin, 2 * i) << ((i & 1) * 16);
-                    }
-                }
-            }
-            v[j] = x;
-        }
-        u32x4 y = v[0];
-        if (coll != AR_COLL_ALLGATHER) {
-            float acc[A];
-            chain(v, acc);
-            y = narrow(acc);
-        }
-#pragma unroll
-        for (int r = 0; r < NMAX; ++r) {
-            if ((uint32_t)r < nout) {
-                const Rsrc rout = out_rsrc(r, nfull_all * 16, (uint64_t)rem * E);
-#pragma unroll
-                for (int i = 0; i < (int)A; ++i) {
-                    if ((uint32_t)i < rem) {
-                        if (E == 4) st32<kOutPol>(rout, 4 * i, y[i]);
-                        else st16<kOutPol>(rout, 2 * i, (y[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu);
-                    }
-                }
-            }
-        }
-    }
-}
-
 // ------------------------------------------------------------------ helpers
 
 __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v)
@@ -1853,28 +1686,12 @@ __host__ bool ll128_wide(const ar_plan_info &info)
     return info.proto == AR_PROTO_LL128 && (info.wave_elems * 4 + 119) / 120 > 16;
 }
 
-// unroll: 16-byte units per thread and iteration.  Two keep more loads in
-// flight, which pays while the data is cache-resident; one streams faster
-// from HBM, where the fastest grid is also small (about 800-1000 waves at
-// 128 MiB x 8 ranks) and keeps fewer DRAM streams open.
-__host__ RingFn direct_fn(int dtype, int nranks, int unroll)
-{
-    if (dtype == AR_FLOAT32) {
-        if (nranks > 8) return direct_kernel<AR_FLOAT32, 16, 1>;
-        return unroll == 2 ? direct_kernel<AR_FLOAT32, 8, 2> : direct_kernel<AR_FLOAT32, 8, 1>;
-    }
-    if (nranks > 8) return direct_kernel<AR_BFLOAT16, 16, 1>;
-    return unroll == 2 ? direct_kernel<AR_BFLOAT16, 8, 2> : direct_kernel<AR_BFLOAT16, 8, 1>;
-}
-
 }  // namespace dev
 
 int launch_ring(const ar_plan_info &info, const RingArgs &args, void *stream)
 {
-    dev::RingFn fn = info.algo == AR_ALGO_DIRECT ? dev::direct_fn(info.dtype, info.nranks, info.direct_unroll)
-                                                 : dev::ring_fn(info.proto, info.dtype, info.peer_direct != 0,
-                                                                args.debug != 0, dev::ll128_wide(info),
-                                                                args.ll128_ordered != 0);
+    dev::RingFn fn = dev::ring_fn(info.proto, info.dtype, info.peer_direct != 0, args.debug != 0,
+                                  dev::ll128_wide(info), args.ll128_ordered != 0);
     if (!fn) return AR_ERR_UNSUPPORTED;
     RingArgs a = args;
     void *kargs[] = {&a};

@@ -72,7 +72,7 @@ extern "C" int ar_run_noalloc(const ar_plan_desc *desc, const void *const *send,
     if (g.algo != AR_ALGO_RING) {
         // The direct algorithm uses no memory besides the rank buffers.
         fill_args(g, d, (uint64_t)tus * kTicksPerUs, send, recv, nullptr, nullptr, nullptr, &a);
-        return ret(launch_ring(g, a, stream));
+        return ret(launch_direct(g, a, stream));
     }
     size_t flags_off = 0, fifo_off = 0;
     const size_t need = workspace_layout(g, &flags_off, &fifo_off);

@@ -188,7 +188,7 @@ namespace {
 // from overlapping; the others wait for no workgroup.
 int launch_gated(int dev, const ar_plan_info &g, const ar_plan_desc &d, const RingArgs &a, void *stream)
 {
-    if (g.algo != AR_ALGO_RING) return launch_ring(g, a, stream);
+    if (g.algo != AR_ALGO_RING) return launch_direct(g, a, stream);
     if (links_in_lds(g, d)) return launch_ring_lds(g, a, stream);
     RingGate<HipGateApi>::Ticket t;
     int rc = g_ring_gate.before(dev, (hipStream_t)stream, t);

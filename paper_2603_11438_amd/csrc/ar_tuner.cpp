@@ -183,8 +183,8 @@ int default_depth(int proto) { return proto == AR_PROTO_SIMPLE ? 2 : 4; }
 constexpr int kMaxDepth = 16;
 constexpr uint64_t kSmallFifoBytes = 4ull << 20;
 
-// Direct algorithm: units (16 bytes of data) per thread per iteration, and
-// the largest grid it is sized to (8 workgroups per CU on 256 CUs).
+// The largest grid the direct algorithm is sized to (8 workgroups per CU on
+// 256 CUs).
 // Direct algorithm: two units per thread and iteration up to this many bytes
 // per rank, one above (measured on MI355X: two keep more loads in flight
 // while the data is cache-resident, one streams faster from HBM).
@@ -211,7 +211,19 @@ int resolve_direct(const ar_plan_desc *d, const ar_tune_out *t, ar_plan_info *ou
     const uint64_t full_bytes = d->count * e * (d->coll == AR_COLL_ALLREDUCE ? 1 : N);
     int unroll = d->direct_unroll ? d->direct_unroll : (t && t->direct_unroll ? t->direct_unroll : 0);
     if (unroll == 0) unroll = full_bytes <= kDirectUnrollBytes ? 2 : 1;
-    if (d->nranks > 8) unroll = 1;  // the 9..16-rank kernel keeps one unit per thread
+    uint64_t parts = (uint64_t)(d->nchannels ? d->nchannels : (t ? t->direct_parts : 0));
+    if (d->nranks > 8) {
+        // The 9..16-rank kernels keep one unit per thread; where the tuner
+        // asked for two, its segments get four times the workgroups instead
+        // (16 ranks, 48 MiB, AllReduce: 320-334 us with as many or twice,
+        // 305 us with four times).
+        if (unroll == 2 && !d->direct_unroll && !d->nchannels) parts *= 4;
+        unroll = 1;
+    }
+    // Two ranks' AllGather has one load and two stores per unit, the least
+    // in flight of all: twice the tuner's waves (20 MiB: 14.4 against 12.6
+    // us, 48 MiB: 30.5 against 27 us).
+    if (d->coll == AR_COLL_ALLGATHER && N == 2 && !d->nwaves && nw <= AR_MAX_WAVES / 2) nw *= 2;
     ar_plan_info g = {};
     g.algo = AR_ALGO_DIRECT;
     g.direct_unroll = unroll;
@@ -230,7 +242,6 @@ int resolve_direct(const ar_plan_desc *d, const ar_tune_out *t, ar_plan_info *ou
         return AR_OK;
     }
     const uint64_t seg_units = ceil_div(g.seg_elems, A);
-    uint64_t parts = (uint64_t)(d->nchannels ? d->nchannels : (t ? t->direct_parts : 0));
     if (parts == 0) {
         parts = ceil_div(seg_units, 64 * (uint64_t)nw * (uint64_t)unroll);
         uint64_t cap = kDirectMaxGrid / N;

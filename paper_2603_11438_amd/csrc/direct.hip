@@ -1,0 +1,226 @@
+// The direct (two-shot) algorithm (gfx950), with no links and no waits.
+//
+// Workgroup b works on segment s = b mod N (part b / N of its parts): a
+// thread loads one 16-byte unit of segment s from every rank (ranks s, s+1,
+// ..., s+N-1 in that order), sums them in that chain order -- the same
+// additions, in the same order, as the ring's reduce-scatter -- and stores
+// the result to every rank.  Every element is read once per rank and written
+// once per rank: the compulsory 2 N S bytes.  In place is safe: each element
+// is read and then written by the same thread.
+//
+// The same kernel runs the other collectives: ReduceScatter sums block s
+// along the chain that starts at rank s+1 (the ring's order for a block that
+// ends at rank s) and writes it to rank s only; AllGather copies rank s's
+// block to block s of every rank.
+//
+// What bounds it.  Small messages: launch and the way to the first load, so
+// the rank count and the collective are template arguments (no divisions, no
+// tests of either, one round of scalar loads: 8 ranks, 4 KiB fp32, 3.0 us as
+// one kernel for all collectives and up to 8 ranks, 2.1 us so), and the
+// partial unit at the end of the data has a workgroup of its own (100003 bf16
+// elements: 8.0 -> 3.1 us).  Large messages: HBM; see units_per_unroll and
+// the loop below for what keeps enough of it in flight.
+#include "ar_device.h"
+
+namespace ar {
+namespace dev {
+
+// What the kernel reads from the kernel argument; sizes in bytes.
+struct DirectArgs {
+    const char *src[AR_MAX_RANKS];
+    char *dst[AR_MAX_RANKS];
+    uint64_t seg;        // a whole segment
+    uint64_t part;       // the whole units of segment full_segs
+    uint32_t full_segs;
+    uint32_t rem;        // elements of the partial unit after them (0: none)
+    uint32_t parts;      // workgroups per segment
+};
+
+// Waves of a workgroup: 256 registers per lane hold a thread's loads and the
+// next ones' without spills.
+constexpr int kMaxDirectWaves = 8;
+
+// Units per thread and iteration for each that the plan asks for (its
+// direct_unroll, 1 or 2): eight ranks have eight loads per unit in flight,
+// fewer ranks and AllGather, which reads one rank per unit, correspondingly
+// less, so they take more units (2 ranks, 48 MiB, bf16, the table's geometry:
+// 72 us with one and two, 35 us with two and four).
+constexpr int units_per_unroll(int n, int coll) { return coll == AR_COLL_ALLGATHER ? 4 : n <= 4 ? 2 : 1; }
+
+// LOOP: a thread has more than one iteration.  Without it the kernel is
+// straight-line code (8 ranks, 4 KiB and 256 KiB, fp32: 2.1 and 2.6 us
+// against 2.2 and 2.75 us).
+template <int DT, int N, int COLL, int U, bool LOOP>
+__global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs a)
+{
+    constexpr uint32_t E = Elem<DT>::E, A = Elem<DT>::A;
+    constexpr int NSRC = COLL == AR_COLL_ALLGATHER ? 1 : N;      // chain length
+    constexpr int NDST = COLL == AR_COLL_REDUCESCATTER ? 1 : N;  // ranks written
+    const uint32_t s = blockIdx.x % N;
+    const uint32_t nth = blockDim.x, tid = threadIdx.x;
+    const bool tail = COLL == AR_COLL_ALLREDUCE && blockIdx.x == a.parts * N;  // see below
+    const uint32_t seg = tail ? a.full_segs : s;
+    // Rank j of the chain, and the place of the segment in its buffers.
+    // AllGather reads, and ReduceScatter writes, one block-sized buffer.
+    const uint32_t first = COLL == AR_COLL_REDUCESCATTER ? s + 1 : seg;
+    auto src_of = [&](int j) {
+        const uint32_t r = first + j;
+        return a.src[r >= N ? r - N : r] + (COLL == AR_COLL_ALLGATHER ? 0 : seg * a.seg);
+    };
+    auto dst_of = [&](int j) {
+        return a.dst[COLL == AR_COLL_REDUCESCATTER ? s : j] + (COLL == AR_COLL_REDUCESCATTER ? 0 : seg * a.seg);
+    };
+
+    if (tail) {
+        // The partial unit at the end of the data: a workgroup of its own,
+        // one lane per element, so that no thread does it on top of its
+        // units, one round trip to memory later.
+        const bool ok = tid < a.rem;
+        float x[N];
+#pragma unroll
+        for (int j = 0; j < NSRC; ++j) {
+            const Rsrc w = make_rsrc(src_of(j) + a.part, (uint64_t)a.rem * E);
+            x[j] = as_f32(E == 4 ? ld32<kInPol>(w, in_range(ok, tid * E)) : ld16<kInPol>(w, in_range(ok, tid * E)) << 16);
+        }
+        float acc = x[0];
+#pragma unroll
+        for (int j = 1; j < NSRC; ++j) acc += x[j];
+        const uint32_t y = E == 4 ? as_u32(acc) : bf16_rne(acc);
+#pragma unroll
+        for (int j = 0; j < NDST; ++j) {
+            const Rsrc w = make_rsrc(dst_of(j) + a.part, (uint64_t)a.rem * E);
+            if (E == 4) st32<kOutPol>(w, in_range(ok, tid * E), y);
+            else st16<kOutPol>(w, in_range(ok, tid * E), y);
+        }
+        return;
+    }
+
+    const uint64_t n = s < a.full_segs ? a.seg : s == a.full_segs ? a.part : 0;
+    const uint32_t span = nth * U * 16;
+    const uint64_t step = (uint64_t)a.parts * span;
+    uint64_t off = (uint64_t)(blockIdx.x / N) * span;
+    if (off >= n) return;
+    u32x4 v[U][NSRC];
+    // Descriptors cover this iteration's bytes; their range check drops the
+    // lanes past the end.
+    auto span_bytes = [&](uint64_t o) { return o >= n ? 0u : n - o < span ? (uint32_t)(n - o) : span; };
+    auto load = [&](uint64_t o) {
+        const uint32_t b = span_bytes(o);
+#pragma unroll
+        for (int j = 0; j < NSRC; ++j) {
+            const Rsrc w = make_rsrc(src_of(j) + o, b);
+#pragma unroll
+            for (int t = 0; t < U; ++t) v[t][j] = ld128<kInPol>(w, (t * nth + tid) * 16);
+        }
+    };
+    auto arrive = [&]() {
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+#pragma unroll
+            for (int j = 0; j < NSRC; ++j) asm volatile("" : "+v"(v[t][j]));
+    };
+    load(off);
+    if (LOOP) arrive();
+    while (true) {
+        u32x4 y[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            if (COLL == AR_COLL_ALLGATHER) {
+                y[t] = v[t][0];  // a copy keeps every bit, NaN payloads included
+            } else if (E == 4) {
+                y[t] = v[t][0];
+#pragma unroll
+                for (int j = 1; j < NSRC; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) y[t][i] = as_u32(as_f32(y[t][i]) + as_f32(v[t][j][i]));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float lo = bf16_lo(v[t][0][i]), hi = bf16_hi(v[t][0][i]);
+#pragma unroll
+                    for (int j = 1; j < NSRC; ++j) {
+                        lo = lo + bf16_lo(v[t][j][i]);
+                        hi = hi + bf16_hi(v[t][j][i]);
+                    }
+                    y[t][i] = pack_bf16(lo, hi);
+                }
+            }
+        }
+        const uint32_t b = span_bytes(off);
+        const uint64_t next = off + step;
+        const bool more = LOOP && next < n;
+        // The next units' loads go out before these units' stores: loads
+        // and stores retire in order, so loads issued after the stores could
+        // only be waited for together with them.
+        if (more) load(next);
+#pragma unroll
+        for (int j = 0; j < NDST; ++j) {
+            const Rsrc w = make_rsrc(dst_of(j) + off, b);
+#pragma unroll
+            for (int t = 0; t < U; ++t) st128<kOutPol>(w, (t * nth + tid) * 16, y[t]);
+        }
+        if (!more) return;
+        arrive();
+        off = next;
+    }
+}
+
+typedef void (*DirectFn)(DirectArgs);
+
+// per_thread: 16-byte units of a segment per thread of its workgroups.
+template <int DT, int COLL, int N = AR_MAX_RANKS>
+__host__ DirectFn direct_fn(int nranks, int unroll, uint64_t per_thread)
+{
+    if constexpr (N >= 2) {
+        if (nranks != N) return direct_fn<DT, COLL, N - 1>(nranks, unroll, per_thread);
+        constexpr int U = units_per_unroll(N, COLL);
+        if constexpr (N <= 8) {
+            if (unroll == 2) return per_thread > 2 * U ? direct_kernel<DT, N, COLL, 2 * U, true>
+                                                         : direct_kernel<DT, N, COLL, 2 * U, false>;
+        }
+        return per_thread > U ? direct_kernel<DT, N, COLL, U, true> : direct_kernel<DT, N, COLL, U, false>;
+    }
+    return nullptr;
+}
+
+template <int DT>
+__host__ DirectFn direct_fn_of(int coll, int nranks, int unroll, uint64_t per_thread)
+{
+    switch (coll) {
+    case AR_COLL_REDUCESCATTER: return direct_fn<DT, AR_COLL_REDUCESCATTER>(nranks, unroll, per_thread);
+    case AR_COLL_ALLGATHER: return direct_fn<DT, AR_COLL_ALLGATHER>(nranks, unroll, per_thread);
+    default: return direct_fn<DT, AR_COLL_ALLREDUCE>(nranks, unroll, per_thread);
+    }
+}
+
+}  // namespace dev
+
+int launch_direct(const ar_plan_info &info, const RingArgs &args, void *stream)
+{
+    const bool f32 = info.dtype == AR_FLOAT32;
+    const uint64_t e = f32 ? 4 : 2;
+    // A plan's workgroup of more than eight waves is launched as two.
+    const uint32_t split = ((uint32_t)info.nwaves + dev::kMaxDirectWaves - 1) / dev::kMaxDirectWaves;
+    const uint32_t threads = 64 * (((uint32_t)info.nwaves + split - 1) / split);
+    const uint32_t parts = (uint32_t)info.nchannels * split;
+    const uint64_t all = (uint64_t)parts * threads, per_thread = (args.seg * e / 16 + all - 1) / all;
+    const dev::DirectFn fn =
+        f32 ? dev::direct_fn_of<AR_FLOAT32>(info.coll, info.nranks, info.direct_unroll, per_thread)
+            : dev::direct_fn_of<AR_BFLOAT16>(info.coll, info.nranks, info.direct_unroll, per_thread);
+    if (!fn) return AR_ERR_UNSUPPORTED;
+    dev::DirectArgs a;
+    for (int r = 0; r < AR_MAX_RANKS; ++r) {
+        a.src[r] = args.src[r];
+        a.dst[r] = args.dst[r];
+    }
+    a.seg = args.seg * e;
+    a.part = args.part * e / 16 * 16;
+    a.full_segs = args.full_segs;
+    a.rem = (uint32_t)(args.part % (16 / e));
+    a.parts = parts;
+    void *kargs[] = {&a};
+    return hipLaunchKernel((const void *)fn, dim3(parts * (unsigned)info.nranks + (a.rem ? 1u : 0u)),
+                           dim3(threads), kargs, 0, (hipStream_t)stream) == hipSuccess ? AR_OK : AR_ERR_HIP;
+}
+
+}  // namespace ar
