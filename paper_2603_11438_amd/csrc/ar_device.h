@@ -25,6 +25,7 @@ constexpr int kFifoLd = kPolSc1;  // device-coherent FIFO reads
 constexpr int kFifoSt = kPolSc1;  // device-coherent FIFO writes
 constexpr int kInPol = kPolNt;    // rank inputs: read once, streamed
 constexpr int kOutPol = kPolNt;   // rank outputs: written once, streamed
+constexpr int kKeepPol = kPolSc1; // rank outputs that the last-level cache holds (outputs_fit_cache)
 static_assert((kFifoLd & kPolSc1) != 0 && (kFifoSt & kPolSc1) != 0, "FIFO accesses must be device-coherent");
 
 template <int DT> struct Elem;

@@ -78,6 +78,25 @@ int launch_copy(const void *src, void *dst, size_t bytes, void *stream);
 int ring_occupancy(int proto, int dtype, int block, int *blocks_per_cu);
 int launch_bf16_round(const float *in, uint16_t *out, size_t n, void *stream);
 
+// How the outputs of a run in LDS or of the direct algorithm are stored.  All
+// ranks' outputs together up to half of the 256 MiB last-level cache: written
+// through the L2 to the memory side (sc1), where that cache takes them, and
+// where the program that reads them next finds them.  Stores with the
+// non-temporal hint would go on to HBM, and what they leave in the L2 is
+// written back at the end of the kernel while everything waits (8 ranks,
+// AllReduce, device time, non-temporal against sc1: 256 KiB fp32 3.0 and 2.2
+// us, 1 MiB bf16 4.2 and 3.3 us, 8 MiB fp32 24.8 and 21.9 us; AllGather of
+// 12 MiB 20.8 and 17.4 us; ReduceScatter of 64 MiB bf16 104.7 and 97.1 us;
+// the other way round only near 16 MiB in all, 6.0 and 6.2 us).  More: the
+// hint, which keeps them from driving each other and the inputs out (20 MiB
+// bf16 58.4 and 61.8 us, 32 MiB 92.8 and 97 us, 64 MiB fp32 186 and 196 us).
+inline bool outputs_fit_cache(const ar_plan_info &g)
+{
+    const uint64_t rank = g.count * (g.dtype == AR_FLOAT32 ? 4 : 2) *
+                          (g.coll == AR_COLL_ALLGATHER ? (uint64_t)g.nranks : 1);
+    return rank * (uint64_t)g.nranks <= (128ull << 20);
+}
+
 // Run-time helpers of ar_runtime.cpp.
 // Where a ring plan's links are.  In LDS, unless the plan asks for links in
 // memory: FIFO-only plans, and plans with debug flags, whose hooks (skipped

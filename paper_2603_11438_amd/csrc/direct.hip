@@ -47,13 +47,15 @@ constexpr int kMaxDirectWaves = 8;
 // 72 us with one and two, 35 us with two and four).
 constexpr int units_per_unroll(int n, int coll) { return coll == AR_COLL_ALLGATHER ? 4 : n <= 4 ? 2 : 1; }
 
+// KEEP: the outputs fit the last-level cache (outputs_fit_cache).
 // LOOP: a thread has more than one iteration.  Without it the kernel is
 // straight-line code (8 ranks, 4 KiB and 256 KiB, fp32: 2.1 and 2.6 us
 // against 2.2 and 2.75 us).
-template <int DT, int N, int COLL, int U, bool LOOP>
+template <int DT, int N, int COLL, int U, bool LOOP, bool KEEP>
 __global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs a)
 {
     constexpr uint32_t E = Elem<DT>::E, A = Elem<DT>::A;
+    constexpr int kOut = KEEP ? kKeepPol : kOutPol;
     constexpr int NSRC = COLL == AR_COLL_ALLGATHER ? 1 : N;      // chain length
     constexpr int NDST = COLL == AR_COLL_REDUCESCATTER ? 1 : N;  // ranks written
     const uint32_t s = blockIdx.x % N;
@@ -89,8 +91,8 @@ __global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs
 #pragma unroll
         for (int j = 0; j < NDST; ++j) {
             const Rsrc w = make_rsrc(dst_of(j) + a.part, (uint64_t)a.rem * E);
-            if (E == 4) st32<kOutPol>(w, in_range(ok, tid * E), y);
-            else st16<kOutPol>(w, in_range(ok, tid * E), y);
+            if (E == 4) st32<kOut>(w, in_range(ok, tid * E), y);
+            else st16<kOut>(w, in_range(ok, tid * E), y);
         }
         return;
     }
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs
         for (int j = 0; j < NDST; ++j) {
             const Rsrc w = make_rsrc(dst_of(j) + off, b);
 #pragma unroll
-            for (int t = 0; t < U; ++t) st128<kOutPol>(w, (t * nth + tid) * 16, y[t]);
+            for (int t = 0; t < U; ++t) st128<kOut>(w, (t * nth + tid) * 16, y[t]);
         }
         if (!more) return;
         arrive();
@@ -168,28 +170,28 @@ __global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs
 typedef void (*DirectFn)(DirectArgs);
 
 // per_thread: 16-byte units of a segment per thread of its workgroups.
-template <int DT, int COLL, int N = AR_MAX_RANKS>
+template <int DT, int COLL, bool KEEP, int N = AR_MAX_RANKS>
 __host__ DirectFn direct_fn(int nranks, int unroll, uint64_t per_thread)
 {
     if constexpr (N >= 2) {
-        if (nranks != N) return direct_fn<DT, COLL, N - 1>(nranks, unroll, per_thread);
+        if (nranks != N) return direct_fn<DT, COLL, KEEP, N - 1>(nranks, unroll, per_thread);
         constexpr int U = units_per_unroll(N, COLL);
         if constexpr (N <= 8) {
-            if (unroll == 2) return per_thread > 2 * U ? direct_kernel<DT, N, COLL, 2 * U, true>
-                                                         : direct_kernel<DT, N, COLL, 2 * U, false>;
+            if (unroll == 2) return per_thread > 2 * U ? direct_kernel<DT, N, COLL, 2 * U, true, KEEP>
+                                                         : direct_kernel<DT, N, COLL, 2 * U, false, KEEP>;
         }
-        return per_thread > U ? direct_kernel<DT, N, COLL, U, true> : direct_kernel<DT, N, COLL, U, false>;
+        return per_thread > U ? direct_kernel<DT, N, COLL, U, true, KEEP> : direct_kernel<DT, N, COLL, U, false, KEEP>;
     }
     return nullptr;
 }
 
-template <int DT>
+template <int DT, bool KEEP>
 __host__ DirectFn direct_fn_of(int coll, int nranks, int unroll, uint64_t per_thread)
 {
     switch (coll) {
-    case AR_COLL_REDUCESCATTER: return direct_fn<DT, AR_COLL_REDUCESCATTER>(nranks, unroll, per_thread);
-    case AR_COLL_ALLGATHER: return direct_fn<DT, AR_COLL_ALLGATHER>(nranks, unroll, per_thread);
-    default: return direct_fn<DT, AR_COLL_ALLREDUCE>(nranks, unroll, per_thread);
+    case AR_COLL_REDUCESCATTER: return direct_fn<DT, AR_COLL_REDUCESCATTER, KEEP>(nranks, unroll, per_thread);
+    case AR_COLL_ALLGATHER: return direct_fn<DT, AR_COLL_ALLGATHER, KEEP>(nranks, unroll, per_thread);
+    default: return direct_fn<DT, AR_COLL_ALLREDUCE, KEEP>(nranks, unroll, per_thread);
     }
 }
 
@@ -204,9 +206,10 @@ int launch_direct(const ar_plan_info &info, const RingArgs &args, void *stream)
     const uint32_t threads = 64 * (((uint32_t)info.nwaves + split - 1) / split);
     const uint32_t parts = (uint32_t)info.nchannels * split;
     const uint64_t all = (uint64_t)parts * threads, per_thread = (args.seg * e / 16 + all - 1) / all;
-    const dev::DirectFn fn =
-        f32 ? dev::direct_fn_of<AR_FLOAT32>(info.coll, info.nranks, info.direct_unroll, per_thread)
-            : dev::direct_fn_of<AR_BFLOAT16>(info.coll, info.nranks, info.direct_unroll, per_thread);
+    const bool keep = outputs_fit_cache(info);
+    const auto pick = f32 ? (keep ? dev::direct_fn_of<AR_FLOAT32, true> : dev::direct_fn_of<AR_FLOAT32, false>)
+                          : (keep ? dev::direct_fn_of<AR_BFLOAT16, true> : dev::direct_fn_of<AR_BFLOAT16, false>);
+    const dev::DirectFn fn = pick(info.coll, info.nranks, info.direct_unroll, per_thread);
     if (!fn) return AR_ERR_UNSUPPORTED;
     dev::DirectArgs a;
     for (int r = 0; r < AR_MAX_RANKS; ++r) {

@@ -60,12 +60,14 @@ struct LdsShape {
     static constexpr uint32_t kPieceBytes = 64 * U * 16;
 };
 
-template <int DT, int N, int COLL>
+// KEEP: the outputs fit the last-level cache (outputs_fit_cache).
+template <int DT, int N, int COLL, bool KEEP>
 __global__ __launch_bounds__(64 * N) void lds_ring_kernel(RingArgs a)
 {
     constexpr int U = LdsShape<N, COLL>::U;
     constexpr uint32_t PB = LdsShape<N, COLL>::kPieceBytes;
     constexpr uint32_t E = Elem<DT>::E, A = Elem<DT>::A;
+    constexpr int kOut = KEEP ? kKeepPol : kOutPol;
     constexpr bool kReduce = COLL != AR_COLL_ALLGATHER;
     constexpr int IN = kReduce ? N : 1;            // segments read per piece
     constexpr int PV = kReduce ? (int)A / 4 : 1;   // 16-byte vectors of a unit on the link
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(64 * N) void lds_ring_kernel(RingArgs a)
         // ReduceScatter writes one block-sized buffer.
         const Rsrc w = window(dst + off + (COLL == AR_COLL_REDUCESCATTER ? 0 : s * full_b), s, full, part);
 #pragma unroll
-        for (int t = 0; t < U; ++t) st128<kOutPol>(w, (64 * t + lane) * 16, y[t]);
+        for (int t = 0; t < U; ++t) st128<kOut>(w, (64 * t + lane) * 16, y[t]);
     };
     // Inputs are waited for in one place, where only stores have been issued
     // after them: loads and stores retire in order, so the compiler, which
@@ -254,8 +256,8 @@ __global__ __launch_bounds__(64 * N) void lds_ring_kernel(RingArgs a)
 #pragma unroll
             for (int i = 0; i < (int)A; ++i) {
                 const uint32_t o = in_range((uint32_t)i < rem && lane == rem_lane, i * E);
-                if (E == 4) st32<kOutPol>(w, o, rem_y[i]);
-                else st16<kOutPol>(w, o, (rem_y[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu);
+                if (E == 4) st32<kOut>(w, o, rem_y[i]);
+                else st16<kOut>(w, o, (rem_y[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu);
             }
         }
         if (kPrefetch) arrive(in);
@@ -267,24 +269,24 @@ __global__ __launch_bounds__(64 * N) void lds_ring_kernel(RingArgs a)
 
 typedef void (*RingFn)(RingArgs);
 
-template <int DT, int COLL, int N = AR_MAX_RANKS>
+template <int DT, int COLL, bool KEEP, int N = AR_MAX_RANKS>
 __host__ RingFn lds_fn(int nranks, uint32_t *piece)
 {
     if constexpr (N >= 2) {
-        if (nranks != N) return lds_fn<DT, COLL, N - 1>(nranks, piece);
+        if (nranks != N) return lds_fn<DT, COLL, KEEP, N - 1>(nranks, piece);
         *piece = LdsShape<N, COLL>::kPieceBytes;
-        return lds_ring_kernel<DT, N, COLL>;
+        return lds_ring_kernel<DT, N, COLL, KEEP>;
     }
     return nullptr;
 }
 
-template <int DT>
+template <int DT, bool KEEP>
 __host__ RingFn lds_fn_of(int coll, int nranks, uint32_t *piece)
 {
     switch (coll) {
-    case AR_COLL_REDUCESCATTER: return lds_fn<DT, AR_COLL_REDUCESCATTER>(nranks, piece);
-    case AR_COLL_ALLGATHER: return lds_fn<DT, AR_COLL_ALLGATHER>(nranks, piece);
-    default: return lds_fn<DT, AR_COLL_ALLREDUCE>(nranks, piece);
+    case AR_COLL_REDUCESCATTER: return lds_fn<DT, AR_COLL_REDUCESCATTER, KEEP>(nranks, piece);
+    case AR_COLL_ALLGATHER: return lds_fn<DT, AR_COLL_ALLGATHER, KEEP>(nranks, piece);
+    default: return lds_fn<DT, AR_COLL_ALLREDUCE, KEEP>(nranks, piece);
     }
 }
 
@@ -297,9 +299,10 @@ constexpr uint64_t kLargeInputBytes = 128ull << 20;
 int launch_ring_lds(const ar_plan_info &info, const RingArgs &args, void *stream)
 {
     uint32_t piece = 0;
-    const dev::RingFn fn = info.dtype == AR_FLOAT32
-                               ? dev::lds_fn_of<AR_FLOAT32>(info.coll, info.nranks, &piece)
-                               : dev::lds_fn_of<AR_BFLOAT16>(info.coll, info.nranks, &piece);
+    const bool f32 = info.dtype == AR_FLOAT32, keep = outputs_fit_cache(info);
+    const auto pick = f32 ? (keep ? dev::lds_fn_of<AR_FLOAT32, true> : dev::lds_fn_of<AR_FLOAT32, false>)
+                          : (keep ? dev::lds_fn_of<AR_BFLOAT16, true> : dev::lds_fn_of<AR_BFLOAT16, false>);
+    const dev::RingFn fn = pick(info.coll, info.nranks, &piece);
     if (!fn) return AR_ERR_UNSUPPORTED;
     // The plan's C * N workgroups, one ring each.  Not more than there are
     // pieces.  And where the inputs together exceed half the last-level
@@ -309,7 +312,7 @@ int launch_ring_lds(const ar_plan_info &info, const RingArgs &args, void *stream
     // us, 32 MiB 101 and 104 us), while a message that the cache holds gains
     // from the second workgroup per compute unit (8 MiB 24.8 and 23.9 us,
     // 4 MiB 13.1 and 12.1 us).
-    const uint64_t seg_b = args.seg * (info.dtype == AR_FLOAT32 ? 4 : 2), n = (uint64_t)info.nranks;
+    const uint64_t seg_b = args.seg * (f32 ? 4 : 2), n = (uint64_t)info.nranks;
     const uint64_t pieces = (seg_b + piece - 1) / piece;
     uint64_t grid = (uint64_t)info.nchannels * n;
     if (pieces < grid) grid = pieces;
