@@ -16,6 +16,7 @@ from typing import Optional, Sequence
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "_lib", "libar.so")
+TENSOR_ARGS_PATH = os.path.join(_PKG, "_lib", "_tensor_args.so")
 
 # ---- constants (include/ar.h) -------------------------------------------
 AR_VERSION = 4  # the interface revision include/ar.h declares
@@ -333,6 +334,47 @@ def _stream_ptr(stream) -> Optional[int]:
     return stream.cuda_stream
 
 
+class _Native:
+    """The native call path (csrc/tensor_args.cpp) and the addresses of the
+    functions it calls.  Checks that are not plainly passed there (call
+    returns -1) are made in Python, which accepts or raises."""
+
+    def __init__(self):
+        import importlib.util
+
+        import torch  # the extension's symbols come from torch's libraries
+
+        if not os.path.exists(TENSOR_ARGS_PATH):
+            raise ImportError(f"the native part of the binding is not built ({TENSOR_ARGS_PATH} missing); "
+                              "run __graft_entry__.build()")
+        spec = importlib.util.spec_from_file_location("_tensor_args", TENSOR_ARGS_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        L = lib()
+        self.call, self.call_bound = mod.call, mod.call_bound
+        self.run, self.run_oop, self.run_noalloc = (
+            ctypes.cast(f, ctypes.c_void_p).value for f in (L.ar_run, L.ar_run_oop, L.ar_run_noalloc))
+        # whether torch has a device context: only then are there device
+        # tensors, and asking for the current stream starts nothing
+        self.in_use = torch.cuda.is_initialized
+        self.device, self.raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+    def stream(self, stream) -> int:
+        """The stream a call goes to: the given one, or the current stream of
+        the current device."""
+        return self.raw_stream(self.device()) if stream is None else stream.cuda_stream
+
+
+_native_path = None
+
+
+def _native() -> _Native:
+    global _native_path
+    if _native_path is None:
+        _native_path = _Native()
+    return _native_path
+
+
 def _ptr_array(tensors: Sequence) -> ctypes.Array:
     arr = (ctypes.c_void_p * max(len(tensors), 1))()
     for i, t in enumerate(tensors):
@@ -370,6 +412,11 @@ class Plan:
         info = ar_plan_info()
         _check(L.ar_plan_get_info(self._h, ctypes.byref(info)), "ar_plan_get_info")
         self.info = info.as_dict()
+        # what the native call path checks the tensors against
+        block, full = self.info["count"], self._full
+        self._expect = (self.info["nranks"], block if self.info["coll"] == AR_COLL_ALLGATHER else full,
+                        block if self.info["coll"] == AR_COLL_REDUCESCATTER else full,
+                        int(self.info["dtype"] == AR_BFLOAT16))
 
     @property
     def handle(self):
@@ -377,14 +424,26 @@ class Plan:
 
     def run(self, tensors: Sequence, stream=None) -> None:
         """In-place collective over a list of N device tensors (each the full buffer)."""
+        n, _, _, bf16 = self._expect
+        nat = _native()
+        if nat.in_use():
+            rc = nat.call(nat.run, self._h.value or 0, tensors, None, n, self._full, 0, bf16, nat.stream(stream))
+            if rc >= 0:
+                return _check(rc, "ar_run")
         self._check_tensors(tensors, self._full)
         rc = lib().ar_run(self._h, _ptr_array(tensors), _stream_ptr(stream))
         _check(rc, "ar_run")
 
     def run_oop(self, send: Sequence, recv: Sequence, stream=None) -> None:
-        coll = self.info["coll"]
-        self._check_tensors(send, self.info["count"] if coll == AR_COLL_ALLGATHER else self._full)
-        self._check_tensors(recv, self.info["count"] if coll == AR_COLL_REDUCESCATTER else self._full)
+        n, send_numel, recv_numel, bf16 = self._expect
+        nat = _native()
+        if recv is not None and nat.in_use():
+            rc = nat.call(nat.run_oop, self._h.value or 0, send, recv, n, send_numel, recv_numel, bf16,
+                          nat.stream(stream))
+            if rc >= 0:
+                return _check(rc, "ar_run_oop")
+        self._check_tensors(send, send_numel)
+        self._check_tensors(recv, recv_numel)
         rc = lib().ar_run_oop(self._h, _ptr_array(send), _ptr_array(recv), _stream_ptr(stream))
         _check(rc, "ar_run_oop")
 
@@ -402,22 +461,18 @@ class Plan:
             self._check_tensors(recv, self.info["count"] if coll == AR_COLL_REDUCESCATTER else self._full)
         sp = _ptr_array(send)
         rp = None if recv is None else _ptr_array(recv)
-        st = _stream_ptr(stream)
-        L = lib()
-        keep = (list(send), None if recv is None else list(recv))
+        st = _stream_ptr(stream) or 0
+        nat = _native()
+        invoke, fn, what = nat.call_bound, nat.run if recv is None else nat.run_oop, "ar_run" if recv is None else "ar_run_oop"
+        sa, ra = ctypes.addressof(sp), 0 if rp is None else ctypes.addressof(rp)
         plan = self
 
-        if recv is None:
-            def call():
-                rc = L.ar_run(plan._h, sp, st)
-                if rc:
-                    _check(rc, "ar_run")
-        else:
-            def call():
-                rc = L.ar_run_oop(plan._h, sp, rp, st)
-                if rc:
-                    _check(rc, "ar_run_oop")
-        call.tensors = keep
+        def call():
+            rc = invoke(fn, plan._h.value or 0, sa, ra, st)
+            if rc:
+                _check(rc, what)
+        call.tensors = (list(send), None if recv is None else list(recv))
+        call.pointers = (sp, rp)
         return call
 
     @property
@@ -548,6 +603,12 @@ def run_noalloc(send: Sequence, recv: Optional[Sequence] = None, stream=None, **
     recv_n = count if coll == AR_COLL_REDUCESCATTER else full
     if len(send) != n or len(recv) != n:
         raise ValueError(f"expected {n} send and {n} recv tensors")
+    nat = _native()
+    if nat.in_use():
+        rc = nat.call(nat.run_noalloc, ctypes.addressof(d), send, recv, n, send_n, recv_n,
+                      int(d.dtype == AR_BFLOAT16), nat.stream(stream))
+        if rc >= 0:
+            return _check(rc, "ar_run_noalloc")
     for t, numel in [(t, send_n) for t in send] + [(t, recv_n) for t in recv]:
         if not t.is_cuda or not t.is_contiguous() or _dtype_of(t) != d.dtype or t.numel() != numel:
             raise ValueError("each tensor must be a contiguous device tensor of the collective's size and dtype")

@@ -1,4 +1,5 @@
-"""Compile libar.so (HIP for gfx950) in-tree with hipcc."""
+"""Compile libar.so (HIP for gfx950) in-tree with hipcc, and the native part of
+the Python binding with g++."""
 from __future__ import annotations
 
 import os
@@ -33,8 +34,10 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every HIP/C++ source of libar into _lib/libar.so (always rebuilds)."""
+    """Compile every HIP/C++ source of libar into _lib/libar.so, and the native
+    part of the Python binding (always rebuilds)."""
     os.makedirs(LIBDIR, exist_ok=True)
+    args_job = start_tensor_args()
     tmp = LIB + ".tmp"
     with tempfile.TemporaryDirectory() as objdir:
         # One compiler per source, at the same time; then one link.
@@ -57,7 +60,38 @@ def build(verbose: bool = False) -> str:
     if verbose and lines:
         print("\n".join(lines))
     os.replace(tmp, LIB)
+    finish_tensor_args(args_job)
     return LIB
+
+
+TENSOR_ARGS_SRC = os.path.join(CSRC, "tensor_args.cpp")
+TENSOR_ARGS = os.path.join(LIBDIR, "_tensor_args.so")
+
+
+def start_tensor_args() -> subprocess.Popen:
+    """Start compiling the native part of the Python binding against torch's
+    headers (its symbols come from the torch that the caller has imported)."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    import torch
+
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", sysconfig.get_paths()["include"],
+           *[a for d in cpp_extension.include_paths() for a in ("-I", d)], TENSOR_ARGS_SRC,
+           *[a for d in cpp_extension.library_paths() for a in ("-L", d)], "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-o", TENSOR_ARGS + ".tmp"]
+    os.makedirs(LIBDIR, exist_ok=True)
+    return subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
+
+def finish_tensor_args(job: subprocess.Popen) -> str:
+    out = job.communicate()[0]
+    if job.returncode != 0:
+        raise RuntimeError("tensor_args build failed:\n" + (out or ""))
+    os.replace(TENSOR_ARGS + ".tmp", TENSOR_ARGS)
+    return TENSOR_ARGS
 
 
 ABI_CHECK_SRC = os.path.join(ROOT, "tests", "native", "abi_gpu_check.cpp")

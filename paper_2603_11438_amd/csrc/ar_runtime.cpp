@@ -1,6 +1,7 @@
 // Plan lifetime, argument checking and launches of libar (C ABI in ar.h).
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <new>
 #include <stdint.h>
 #include <stdlib.h>
@@ -95,14 +96,27 @@ int check_buffers(const ar_plan_info &g, const void *const *send, void *const *r
     return AR_OK;
 }
 
+// Co-resident workgroups of a ring kernel on a device, once asked for: they
+// are properties of the compiled kernels and the device, and the sixteen
+// occupancy queries behind them cost several times what a small collective
+// takes, on every plan and every allocation-free call.
+constexpr int kCapDevices = 16;
+std::atomic<int> g_resident[kCapDevices][3][2][AR_MAX_WAVES];  // workgroups + 1; 0: not asked yet
+
 int device_channel_capacity(int proto, int dtype, int nranks, int nwaves, int *cap)
 {
-    int dev = 0, cus = 0, per_cu = 0;
+    int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return AR_ERR_HIP;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return AR_ERR_HIP;
-    int rc = ring_occupancy(proto, dtype, 64 * nwaves, &per_cu);
-    if (rc != AR_OK) return rc;
-    long total = (long)per_cu * cus;
+    std::atomic<int> *slot = dev >= 0 && dev < kCapDevices ? &g_resident[dev][proto][dtype][nwaves - 1] : nullptr;
+    long total = slot ? slot->load(std::memory_order_relaxed) - 1 : -1;
+    if (total < 0) {
+        int cus = 0, per_cu = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return AR_ERR_HIP;
+        int rc = ring_occupancy(proto, dtype, 64 * nwaves, &per_cu);
+        if (rc != AR_OK) return rc;
+        total = (long)per_cu * cus;
+        if (slot) slot->store((int)total + 1, std::memory_order_relaxed);
+    }
     long ch = total / nranks;
     if (ch > AR_MAX_CHANNELS) ch = AR_MAX_CHANNELS;
     *cap = (int)ch;
