@@ -211,8 +211,9 @@ typedef struct ar_plan_desc {
  *                    events are still pending is not timed.
  *   AR_PLAN_FIFO_ONLY  ring plans: links in memory, every hop through the
  *                    FIFOs.  By default the links are in LDS: the plan's
- *                    nchannels * nranks workgroups are that many rings, and
- *                    chunk_bytes, fifo_depth, nwaves, placement and the
+ *                    nchannels * nranks workgroups of nwaves waves become up
+ *                    to nchannels * nranks * nwaves / 2 rings of one
+ *                    workgroup, and chunk_bytes, fifo_depth, placement and the
  *                    watchdog do not apply.  A plan with debug flags and
  *                    without this one has links in memory in the peer-direct
  *                    mode: the second rank of each reduce-scatter chain

@@ -2,10 +2,9 @@
 //
 // One workgroup holds one whole ring: wave r is rank r, and the link
 // r -> r+1 is a pair of slots in the workgroup's LDS.  A plan's C * N
-// workgroups are C * N such rings (the waves per workgroup that a plan names
-// are those of links in memory), and ring q takes the pieces q, q + C N, ...
-// of every segment, so that neighbouring workgroups touch neighbouring
-// memory.  The schedule is the ring's of
+// workgroups of W waves become up to C * N * W / 2 such rings, R of them; ring
+// q takes the pieces q, q + R, ... of every segment, so that neighbouring
+// workgroups touch neighbouring memory.  The schedule is the ring's of
 // ar_kernels.hip (segment s is summed along the chain x_s + x_{s+1} + ... +
 // x_{s+N-1} while it travels round the reduce-scatter, the last rank of the
 // chain finishes it, and it travels round once more), with the same
@@ -304,21 +303,27 @@ int launch_ring_lds(const ar_plan_info &info, const RingArgs &args, void *stream
                           : (keep ? dev::lds_fn_of<AR_BFLOAT16, true> : dev::lds_fn_of<AR_BFLOAT16, false>);
     const dev::RingFn fn = pick(info.coll, info.nranks, &piece);
     if (!fn) return AR_ERR_UNSUPPORTED;
-    // The plan's C * N workgroups, one ring each.  Not more than there are
-    // pieces.  And where the inputs together exceed half the last-level
-    // cache, not more than fill the compute units once (256 workgroups, or
-    // 2048 waves): more only widen the stretch of memory that is open at a
-    // time (8 ranks, fp32, 256 against 512 workgroups: 128 MiB 385 and 400
-    // us, 32 MiB 101 and 104 us), while a message that the cache holds gains
-    // from the second workgroup per compute unit (8 MiB 24.8 and 23.9 us,
-    // 4 MiB 13.1 and 12.1 us).
+    // The plan's C * N workgroups of W waves become C * N * W / 2 rings (the
+    // Simple default of 16 channels of 4 waves, 8 ranks, bf16, 9 MiB: 37.9 us
+    // with C * N rings, 30.2 with these).  Not more than there are pieces, and
+    // not more than fill the compute units twice (512 workgroups, more of few
+    // ranks); where the inputs together exceed half the last-level cache,
+    // once: more only widen the stretch of memory that is open at a time (8
+    // ranks, fp32, 256 against 512 workgroups: 128 MiB 385 and 400 us, 32 MiB
+    // 101 and 104 us), while a message that the cache holds gains from the
+    // second workgroup per compute unit (8 MiB 24.8 and 23.9 us, 4 MiB 13.1
+    // and 12.1 us).  Beyond 256 a multiple of 256, as many on each compute
+    // unit (bf16, 5 ranks, 16 MiB, 255 / 320 / 380 / 510 workgroups: 31.8 /
+    // 41.0 / 33.9 / 31.5 us; 7 ranks, 48 MiB, 252 and 292: 164 and 204 us; 3
+    // ranks, 48 MiB, 510 and 600: 56.2 and 61.7 us).
     const uint64_t seg_b = args.seg * (f32 ? 4 : 2), n = (uint64_t)info.nranks;
     const uint64_t pieces = (seg_b + piece - 1) / piece;
-    uint64_t grid = (uint64_t)info.nchannels * n;
-    if (pieces < grid) grid = pieces;
     const uint64_t in_b = seg_b * n * (info.coll == AR_COLL_ALLGATHER ? 1 : n);
-    const uint64_t once = n < 8 ? 2048 / n : 256;
-    if (in_b > kLargeInputBytes && grid > once) grid = once;
+    const uint64_t once = n == 2 ? 1024 : n < 5 ? 512 : 256, most = in_b > kLargeInputBytes ? once : 2 * once;
+    uint64_t grid = (uint64_t)info.nchannels * n * (((uint64_t)info.nwaves + 1) / 2);
+    if (grid > most) grid = most;
+    if (grid > 256) grid -= grid % 256;
+    if (grid > pieces) grid = pieces;
     RingArgs a = args;
     void *kargs[] = {&a};
     return hipLaunchKernel((const void *)fn, dim3((unsigned)grid), dim3(64u * (unsigned)n), kargs, 0,

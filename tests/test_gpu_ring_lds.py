@@ -35,7 +35,7 @@ def _piece_units(n, coll="allreduce"):
 @pytest.mark.parametrize("n", range(2, 17))
 def test_allreduce_edges(ar, n, dtype):
     """Counts whose last segment ends inside, at and just past a piece, a lane
-    and a unit; one channel, so n rings share the pieces: one piece or fewer
+    and a unit; one channel of one wave, so n rings share the pieces: one piece or fewer
     per ring, and two and three with the next one loaded ahead."""
     a = 4 if dtype == "f32" else 8
     p = _piece_units(n) * a  # elements of a piece
@@ -44,7 +44,7 @@ def test_allreduce_edges(ar, n, dtype):
     for i, count in enumerate(counts):
         x = draw(n, count, dtype, "normal", seed=900 + 31 * n + i)
         proto = ("simple", "ll", "ll128")[i % 3]
-        run_case(ar, x, dtype, f"lds-{n}-{dtype}-{count}-{proto}", proto=proto, nchannels=1)
+        run_case(ar, x, dtype, f"lds-{n}-{dtype}-{count}-{proto}", proto=proto, nchannels=1, nwaves=1)
 
 
 @pytest.mark.parametrize("coll", ("reducescatter", "allgather"))
@@ -66,7 +66,7 @@ def test_blocks_against_links_in_memory(ar, coll, n):
             for flags in (0, ar.AR_PLAN_FIFO_ONLY):
                 say(f"lds {coll} N={n} count={count} {dtype} flags={flags}")
                 recv = [torch.full((nr,), float("nan"), device="cuda:0").to(send[0].dtype) for _ in range(n)]
-                with ar.Plan(n, count, dtype, coll=coll, proto="simple", nchannels=1, flags=flags) as plan:
+                with ar.Plan(n, count, dtype, coll=coll, proto="simple", nchannels=1, nwaves=1, flags=flags) as plan:
                     plan.run_oop(send, recv)
                     full = [torch.zeros(n * count, dtype=t.dtype, device="cuda:0") for t in send]
                     for r in range(n):
@@ -81,6 +81,24 @@ def test_blocks_against_links_in_memory(ar, coll, n):
                     mine = full[r][r * count:(r + 1) * count] if coll == "reducescatter" else full[r]
                     assert np.array_equal(to_bits(recv[r], dtype), want[r]), (coll, n, count, dtype, flags, r)
                     assert np.array_equal(to_bits(mine, dtype), want[r]), (coll, n, count, dtype, flags, r, "in place")
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+@pytest.mark.parametrize("n", (2, 3, 5, 8))
+def test_rings_of_a_plan(ar, n, dtype):
+    """The number of rings follows channels and waves, is a multiple of 256
+    beyond it, and is bounded by the compute units: messages of more pieces
+    than any of these, with the last ones partial."""
+    a = 4 if dtype == "f32" else 8
+    count = n * (2100 if n == 2 else 1030) * _piece_units(n) * a - 7
+    x = draw(n, count, dtype, "normal", seed=40 + n)
+    want = oracle_bits(x, dtype)
+    for channels, waves in ((1, 2), (7, 3), (16, 4), (min(128, 256 // n), 4)):
+        say(f"rings N={n} {dtype} C={channels} W={waves}")
+        with ar.Plan(n, count, dtype, proto="simple", nchannels=channels, nwaves=waves) as plan:
+            ts = to_device(x, dtype)
+            plan.run(ts)
+            assert_ranks_equal(ts, want, dtype, f"rings {n} {channels} {waves}")
 
 
 @pytest.mark.parametrize("dtype", ("f32", "bf16"))
