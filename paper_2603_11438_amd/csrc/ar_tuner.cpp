@@ -212,18 +212,23 @@ int resolve_direct(const ar_plan_desc *d, const ar_tune_out *t, ar_plan_info *ou
     int unroll = d->direct_unroll ? d->direct_unroll : (t && t->direct_unroll ? t->direct_unroll : 0);
     if (unroll == 0) unroll = full_bytes <= kDirectUnrollBytes ? 2 : 1;
     uint64_t parts = (uint64_t)(d->nchannels ? d->nchannels : (t ? t->direct_parts : 0));
+    const uint64_t seg_elems = d->coll == AR_COLL_ALLREDUCE ? round_up(ceil_div(d->count, N), A) : d->count;
+    const uint64_t seg_units = ceil_div(seg_elems, A);
     if (d->nranks > 8) {
         // The 9..16-rank kernels keep one unit per thread; where the tuner
         // asked for two, its segments get four times the workgroups instead
         // (16 ranks, 48 MiB, AllReduce: 320-334 us with as many or twice,
-        // 305 us with four times).
-        if (unroll == 2 && !d->direct_unroll && !d->nchannels) parts *= 4;
+        // 305 us with four times), as far as there is a unit for each.
+        if (unroll == 2 && !d->direct_unroll && !d->nchannels && parts < seg_units)
+            parts = parts * 4 < seg_units ? parts * 4 : seg_units;
         unroll = 1;
     }
     // Two ranks' AllGather has one load and two stores per unit, the least
     // in flight of all: twice the tuner's waves (20 MiB: 14.4 against 12.6
-    // us, 48 MiB: 30.5 against 27 us).
-    if (d->coll == AR_COLL_ALLGATHER && N == 2 && !d->nwaves && nw <= AR_MAX_WAVES / 2) nw *= 2;
+    // us, 48 MiB: 30.5 against 27 us), unless its workgroups already outnumber
+    // the units.
+    if (d->coll == AR_COLL_ALLGATHER && N == 2 && !d->nwaves && nw <= AR_MAX_WAVES / 2 &&
+        (parts < seg_units || seg_units == 0)) nw *= 2;
     ar_plan_info g = {};
     g.algo = AR_ALGO_DIRECT;
     g.direct_unroll = unroll;
@@ -235,13 +240,12 @@ int resolve_direct(const ar_plan_desc *d, const ar_tune_out *t, ar_plan_info *ou
     g.placement = d->placement;
     g.count = d->count;
     g.block = 64 * nw;
-    g.seg_elems = d->coll == AR_COLL_ALLREDUCE ? round_up(ceil_div(d->count, N), A) : d->count;
+    g.seg_elems = seg_elems;
     if (N == 1 || d->count == 0) {
         g.grid = 0;
         *out = g;
         return AR_OK;
     }
-    const uint64_t seg_units = ceil_div(g.seg_elems, A);
     if (parts == 0) {
         parts = ceil_div(seg_units, 64 * (uint64_t)nw * (uint64_t)unroll);
         uint64_t cap = kDirectMaxGrid / N;
