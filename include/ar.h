@@ -423,7 +423,8 @@ typedef struct ar_tune_out {
                               nchannels, chunk_bytes and nwaves describe the
                               ring choice, used whenever the ring runs. */
     int direct_parts;      /* direct algorithm: workgroups per segment
-                              (0 = sized to the message) */
+                              (0 = sized to the message; more than a launch
+                              can hold = one per 16-byte unit) */
     int direct_nwaves;     /* direct algorithm: waves per workgroup (0 = 4) */
     int direct_unroll;     /* direct algorithm: 16-byte units per thread and
                               iteration, 1 or 2 (0 = by size: 2 up to 8 MiB

@@ -78,6 +78,22 @@ int launch_copy(const void *src, void *dst, size_t bytes, void *stream);
 int ring_occupancy(int proto, int dtype, int block, int *blocks_per_cu);
 int launch_bf16_round(const float *in, uint16_t *out, size_t n, void *stream);
 
+// Workgroups of the direct algorithm have at most kMaxDirectWaves waves: a
+// plan's workgroup of more is launched as direct_split workgroups of
+// direct_threads threads.
+constexpr int kMaxDirectWaves = 8;
+constexpr uint32_t direct_split(int nwaves) { return ((uint32_t)nwaves + kMaxDirectWaves - 1) / kMaxDirectWaves; }
+constexpr uint32_t direct_threads(int nwaves)
+{
+    return 64 * (((uint32_t)nwaves + direct_split(nwaves) - 1) / direct_split(nwaves));
+}
+// The most workgroups per segment that one launch can hold: fewer than 2^32
+// threads in all, with one workgroup left for the partial unit.
+constexpr uint64_t direct_max_parts(int nranks, int nwaves)
+{
+    return (0xFFFFFFFFull / direct_threads(nwaves) - 1) / (direct_split(nwaves) * (uint64_t)nranks);
+}
+
 // How the outputs of a run in LDS or of the direct algorithm are stored.  All
 // ranks' outputs together up to half of the 256 MiB last-level cache: written
 // through the L2 to the memory side (sc1), where that cache takes them, and

@@ -253,6 +253,10 @@ int resolve_direct(const ar_plan_desc *d, const ar_tune_out *t, ar_plan_info *ou
         if (parts > cap) parts = cap;
         if (parts < 1) parts = 1;
     }
+    // A number of workgroups that no launch can hold stands for one per unit
+    // of the segment (more have nothing to do), as far as a launch holds those.
+    const uint64_t most = direct_max_parts(d->nranks, nw);
+    if (parts > most) parts = seg_units < most ? seg_units : most;
     g.nchannels = (int)parts;
     g.grid = (int)(parts * N);
     g.chan_elems = round_up(ceil_div(g.seg_elems, parts), A);

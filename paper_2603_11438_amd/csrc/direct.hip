@@ -36,10 +36,6 @@ struct DirectArgs {
     uint32_t parts;      // workgroups per segment
 };
 
-// Waves of a workgroup: 256 registers per lane hold a thread's loads and the
-// next ones' without spills.
-constexpr int kMaxDirectWaves = 8;
-
 // Units per thread and iteration for each that the plan asks for (its
 // direct_unroll, 1 or 2): eight ranks have eight loads per unit in flight,
 // fewer ranks and AllGather, which reads one rank per unit, correspondingly
@@ -51,6 +47,8 @@ constexpr int units_per_unroll(int n, int coll) { return coll == AR_COLL_ALLGATH
 // LOOP: a thread has more than one iteration.  Without it the kernel is
 // straight-line code (8 ranks, 4 KiB and 256 KiB, fp32: 2.1 and 2.6 us
 // against 2.2 and 2.75 us).
+// kMaxDirectWaves: 256 registers per lane hold a thread's loads and the next
+// ones' without spills.
 template <int DT, int N, int COLL, int U, bool LOOP, bool KEEP>
 __global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs a)
 {
@@ -201,10 +199,10 @@ int launch_direct(const ar_plan_info &info, const RingArgs &args, void *stream)
 {
     const bool f32 = info.dtype == AR_FLOAT32;
     const uint64_t e = f32 ? 4 : 2;
-    // A plan's workgroup of more than eight waves is launched as two.
-    const uint32_t split = ((uint32_t)info.nwaves + dev::kMaxDirectWaves - 1) / dev::kMaxDirectWaves;
-    const uint32_t threads = 64 * (((uint32_t)info.nwaves + split - 1) / split);
-    const uint32_t parts = (uint32_t)info.nchannels * split;
+    // The plan's geometry is at most direct_max_parts per segment, so that
+    // these counts and the grid below fit 32 bits.
+    const uint32_t threads = direct_threads(info.nwaves);
+    const uint32_t parts = (uint32_t)info.nchannels * direct_split(info.nwaves);
     const uint64_t all = (uint64_t)parts * threads, per_thread = (args.seg * e / 16 + all - 1) / all;
     const bool keep = outputs_fit_cache(info);
     const auto pick = f32 ? (keep ? dev::direct_fn_of<AR_FLOAT32, true> : dev::direct_fn_of<AR_FLOAT32, false>)

@@ -69,3 +69,18 @@ def test_blocks(ar, n, dtype):
         whole = np.concatenate([to_bits(b, dtype) for b in blocks])
         for r in range(n):
             assert np.array_equal(to_bits(full[r], dtype), whole), ("allgather", n, count, cfg, r)
+
+
+@pytest.mark.parametrize("n", (8, 16))
+def test_more_workgroups_than_a_launch_holds(ar, n):
+    """A tuner's number of workgroups that no launch can hold: the plan is
+    bounded by the segment's units and every element is summed."""
+    count = 1001
+    x = draw(n, count, "f32", "normal", seed=71)
+    ar.ar_set_tuner(lambda ctx: {"algo": ar.AR_ALGO_DIRECT, "direct_parts": 1 << 28, "direct_nwaves": 16})
+    try:
+        info = ar.ar_plan_geometry(ar.make_desc(n, count, "f32"))
+        assert 0 < info["nchannels"] <= 32
+        run_case(ar, x, "f32", f"direct-{n}-bounded")
+    finally:
+        ar.ar_set_tuner(None)
