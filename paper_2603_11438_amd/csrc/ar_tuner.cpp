@@ -214,21 +214,7 @@ int resolve_direct(const ar_plan_desc *d, const ar_tune_out *t, ar_plan_info *ou
     uint64_t parts = (uint64_t)(d->nchannels ? d->nchannels : (t ? t->direct_parts : 0));
     const uint64_t seg_elems = d->coll == AR_COLL_ALLREDUCE ? round_up(ceil_div(d->count, N), A) : d->count;
     const uint64_t seg_units = ceil_div(seg_elems, A);
-    if (d->nranks > 8) {
-        // The 9..16-rank kernels keep one unit per thread; where the tuner
-        // asked for two, its segments get four times the workgroups instead
-        // (16 ranks, 48 MiB, AllReduce: 320-334 us with as many or twice,
-        // 305 us with four times), as far as there is a unit for each.
-        if (unroll == 2 && !d->direct_unroll && !d->nchannels && parts < seg_units)
-            parts = parts * 4 < seg_units ? parts * 4 : seg_units;
-        unroll = 1;
-    }
-    // Two ranks' AllGather has one load and two stores per unit, the least
-    // in flight of all: twice the tuner's waves (20 MiB: 14.4 against 12.6
-    // us, 48 MiB: 30.5 against 27 us), unless its workgroups already outnumber
-    // the units.
-    if (d->coll == AR_COLL_ALLGATHER && N == 2 && !d->nwaves && nw <= AR_MAX_WAVES / 2 &&
-        (parts < seg_units || seg_units == 0)) nw *= 2;
+    if (d->nranks > 8) unroll = 1;  // the kernels of 9..16 ranks have one unit per thread
     ar_plan_info g = {};
     g.algo = AR_ALGO_DIRECT;
     g.direct_unroll = unroll;
@@ -549,6 +535,29 @@ int ar_reload_tuner(ar_tuner_fn fn, void *user, ar_reload_stats *stats)
     return install(fn, user, true, stats);
 }
 
+// What a row's direct columns become where the rank count has a kernel of
+// another shape than the eight ranks they were measured with.  Only for the
+// library's own use of its table: a caller's tuner is taken at its word.
+static void fit_direct_to_ranks(const ar_tune_ctx &c, ar_tune_out *out)
+{
+    const uint64_t e = c.dtype == AR_FLOAT32 ? 4 : 2, n = (uint64_t)c.nranks;
+    const uint64_t units = ceil_div(ceil_div(c.msg_bytes / e, n), 16 / e);  // 16-byte units of a segment
+    const uint64_t parts = (uint64_t)out->direct_parts;
+    if (c.nranks > 8 && out->direct_unroll == 2) {
+        // The kernels of 9..16 ranks have one unit per thread; four times the
+        // workgroups, as far as there is a unit for each, stand for the second
+        // (16 ranks, 48 MiB, AllReduce: 320-334 us with as many or twice, 305
+        // us with four times).
+        if (parts < units) out->direct_parts = (int)(parts * 4 < units ? parts * 4 : units);
+        out->direct_unroll = 1;
+    }
+    // Two ranks' AllGather has one load and two stores per unit, the least
+    // in flight of all: twice the waves (20 MiB: 14.4 against 12.6 us, 48 MiB:
+    // 30.5 against 27 us), unless the workgroups already outnumber the units.
+    if (c.coll == AR_COLL_ALLGATHER && c.nranks == 2 && out->direct_nwaves <= AR_MAX_WAVES / 2 && parts < units)
+        out->direct_nwaves *= 2;
+}
+
 int ar_tune(const ar_tune_ctx *ctx, ar_tune_out *out)
 {
     if (!ctx || !out) return AR_ERR_ARG;
@@ -559,6 +568,7 @@ int ar_tune(const ar_tune_ctx *ctx, ar_tune_out *out)
     TunerSlot *slot = pin_active();
     ar_tune_out t = {AR_PROTO_AUTO, 0, 0, 0, AR_ALGO_AUTO, 0, 0};
     int rc = slot->fn(ctx, &t, slot->user);
+    if (rc == 0 && slot->fn == ar_tuner_table) fit_direct_to_ranks(*ctx, &t);
     unpin(slot);
 
     // No opinion on the protocol means the fixed default's ring choice.

@@ -1,5 +1,6 @@
-"""Workgroups of the direct algorithm for more than eight ranks, where two
-units per thread become four times the workgroups (no GPU)."""
+"""Workgroups and waves of the direct algorithm: a caller's tuner is taken at
+its word, the rows of the built-in table are fitted to the rank count, and no plan
+has more workgroups than a launch holds (no GPU)."""
 from __future__ import annotations
 
 import pytest
@@ -7,19 +8,51 @@ import pytest
 import paper_2603_11438_amd as ar
 
 
-@pytest.mark.parametrize("parts,count,want", [
-    (4, 16 * 4 * 1000, 16),        # four times, with units for all of them
-    (4, 16 * 4 * 9, 9),            # as far as there is a unit for each
-    (32, 16 * 4 * 9, 32),          # the tuner's own number is not lowered
-])
-def test_parts_beyond_eight_ranks(parts, count, want):
+def _geometry(answer, *desc, **kw):
     ar.lib()
-    ar.ar_set_tuner(lambda ctx: {"algo": ar.AR_ALGO_DIRECT, "direct_parts": parts, "direct_unroll": 2})
+    ar.ar_set_tuner(lambda ctx: {"algo": ar.AR_ALGO_DIRECT, **answer})
     try:
-        info = ar.ar_plan_geometry(ar.make_desc(16, count, "f32"))
+        return ar.ar_plan_geometry(ar.make_desc(*desc, **kw))
     finally:
         ar.ar_set_tuner(None)
-    assert info["nchannels"] == want and info["direct_unroll"] == 1
+
+
+@pytest.mark.parametrize("unroll", (0, 1, 2))
+@pytest.mark.parametrize("n,coll,count", [(16, "allreduce", 16 * 4 * 1000), (9, "reducescatter", 4096), (2, "allgather", 4096),
+                                          (2, "allreduce", 99), (8, "allgather", 1 << 20)])
+@pytest.mark.parametrize("parts,waves", [(4, 4), (32, 1), (7, 16)])
+def test_a_tuners_answer_is_kept(parts, waves, n, coll, count, unroll):
+    info = _geometry({"direct_parts": parts, "direct_nwaves": waves, "direct_unroll": unroll}, n, count, "f32", coll=coll)
+    assert (info["nchannels"], info["nwaves"]) == (parts, waves)
+    if n > 8:
+        assert info["direct_unroll"] == 1
+
+
+@pytest.mark.parametrize("dtype", ("f32", "bf16"))
+@pytest.mark.parametrize("coll", ("allreduce", "reducescatter", "allgather"))
+@pytest.mark.parametrize("n", (2, 3, 9, 11, 16))
+def test_table_rows_at_other_rank_counts(n, coll, dtype):
+    """A row's workgroups keep the grid of eight ranks; more than eight ranks
+    take four times as many where the row has two units per thread, as far as
+    there is a unit for each, and a two-rank AllGather twice the waves."""
+    ar.lib()
+    c = ar.COLLS[coll]
+    a = 4 if dtype == "f32" else 8
+    doubled = quadrupled = 0
+    for lg in range(8, 28):
+        for size in (1 << lg, (3 << lg) // 2 // (16 * n) * 16 * n):
+            row = ar.ar_tuner_raw("table", size, 8, dtype, coll=c)
+            got = ar.ar_tune(size, n, dtype, coll=c)
+            units = -(-(-(-(size * a // 16) // n)) // a)
+            parts, waves, unroll = row["direct_parts"], row["direct_nwaves"], row["direct_unroll"]
+            if parts:
+                parts = max(1, (parts * 8 + n // 2) // n)
+            if coll == "allgather" and n == 2 and parts < units:
+                waves, doubled = 2 * waves, doubled + 1
+            if n > 8 and unroll == 2:
+                parts, unroll, quadrupled = max(parts, min(4 * parts, units)), 1, quadrupled + (parts > 0)
+            assert (got["direct_parts"], got["direct_nwaves"], got["direct_unroll"]) == (parts, waves, unroll), size
+    assert (doubled > 0) == (coll == "allgather" and n == 2) and (quadrupled > 0) == (n > 8)
 
 
 @pytest.mark.parametrize("n,count,waves", [(8, 1001, 16), (8, 1001, 4), (16, 16 * 4 * 1000, 4), (16, 1 << 39, 9),
@@ -29,12 +62,7 @@ def test_parts_no_launch_can_hold(parts, n, count, waves):
     """A launch holds fewer than 2^32 threads.  A number of workgroups beyond
     that becomes one per unit of the segment, as far as a launch holds those;
     grid 0 is kept for plans that launch nothing."""
-    ar.lib()
-    ar.ar_set_tuner(lambda ctx: {"algo": ar.AR_ALGO_DIRECT, "direct_parts": parts, "direct_nwaves": waves})
-    try:
-        info = ar.ar_plan_geometry(ar.make_desc(n, count, "f32"))
-    finally:
-        ar.ar_set_tuner(None)
+    info = _geometry({"direct_parts": parts, "direct_nwaves": waves}, n, count, "f32")
     units = -(-(-(-count // n)) // 4)
     split = -(-waves // 8)  # a workgroup of more than eight waves is launched as two
     threads = 64 * -(-waves // split)
