@@ -345,11 +345,14 @@ class _Native:
         import torch  # the extension's symbols come from torch's libraries
 
         if not os.path.exists(TENSOR_ARGS_PATH):
-            raise ImportError(f"the native part of the binding is not built ({TENSOR_ARGS_PATH} missing); "
-                              "run __graft_entry__.build()")
+            raise ImportError(f"not built ({TENSOR_ARGS_PATH} missing); run __graft_entry__.build()")
         spec = importlib.util.spec_from_file_location("_tensor_args", TENSOR_ARGS_PATH)
         mod = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(mod)
+        self.torch_version = mod.torch_version
+        if self.torch_version != str(torch.__version__):
+            # it reads torch's C++ objects as that version laid them out
+            raise ImportError(f"built against torch {self.torch_version}, loaded is {torch.__version__}")
         L = lib()
         self.call, self.call_bound = mod.call, mod.call_bound
         self.run, self.run_oop, self.run_noalloc = (
@@ -365,14 +368,23 @@ class _Native:
         return self.raw_stream(self.device()) if stream is None else stream.cuda_stream
 
 
-_native_path = None
+_native_path = None  # not looked for yet; False: cannot be used
 
 
-def _native() -> _Native:
+def _native() -> Optional[_Native]:
+    """The native call path; None (with a warning, once) where it cannot be
+    used: calls then take the checks in Python and the C call by ctypes."""
     global _native_path
     if _native_path is None:
-        _native_path = _Native()
-    return _native_path
+        try:
+            _native_path = _Native()
+        except (ImportError, AttributeError) as e:  # AttributeError: a torch without devices
+            import warnings
+
+            warnings.warn(f"the native part of the binding cannot be used: {e}; tensors are checked in Python, "
+                          "some 10 us per call", RuntimeWarning, stacklevel=3)
+            _native_path = False
+    return _native_path or None
 
 
 def _ptr_array(tensors: Sequence) -> ctypes.Array:
@@ -426,7 +438,7 @@ class Plan:
         """In-place collective over a list of N device tensors (each the full buffer)."""
         n, _, _, bf16 = self._expect
         nat = _native()
-        if nat.in_use():
+        if nat is not None and nat.in_use():
             rc = nat.call(nat.run, self._h.value or 0, tensors, None, n, self._full, 0, bf16, nat.stream(stream))
             if rc >= 0:
                 return _check(rc, "ar_run")
@@ -437,7 +449,7 @@ class Plan:
     def run_oop(self, send: Sequence, recv: Sequence, stream=None) -> None:
         n, send_numel, recv_numel, bf16 = self._expect
         nat = _native()
-        if recv is not None and nat.in_use():
+        if recv is not None and nat is not None and nat.in_use():
             rc = nat.call(nat.run_oop, self._h.value or 0, send, recv, n, send_numel, recv_numel, bf16,
                           nat.stream(stream))
             if rc >= 0:
@@ -462,15 +474,24 @@ class Plan:
         sp = _ptr_array(send)
         rp = None if recv is None else _ptr_array(recv)
         st = _stream_ptr(stream) or 0
-        nat = _native()
-        invoke, fn, what = nat.call_bound, nat.run if recv is None else nat.run_oop, "ar_run" if recv is None else "ar_run_oop"
-        sa, ra = ctypes.addressof(sp), 0 if rp is None else ctypes.addressof(rp)
+        nat, what = _native(), "ar_run" if recv is None else "ar_run_oop"
         plan = self
+        if nat is not None:
+            invoke, fn = nat.call_bound, nat.run if recv is None else nat.run_oop
+            sa, ra = ctypes.addressof(sp), 0 if rp is None else ctypes.addressof(rp)
 
-        def call():
-            rc = invoke(fn, plan._h.value or 0, sa, ra, st)
-            if rc:
-                _check(rc, what)
+            def call():
+                rc = invoke(fn, plan._h.value or 0, sa, ra, st)
+                if rc:
+                    _check(rc, what)
+        else:
+            fn = lib().ar_run if recv is None else lib().ar_run_oop
+            args = (sp, st) if recv is None else (sp, rp, st)
+
+            def call():
+                rc = fn(plan._h, *args)
+                if rc:
+                    _check(rc, what)
         call.tensors = (list(send), None if recv is None else list(recv))
         call.pointers = (sp, rp)
         return call
@@ -604,7 +625,7 @@ def run_noalloc(send: Sequence, recv: Optional[Sequence] = None, stream=None, **
     if len(send) != n or len(recv) != n:
         raise ValueError(f"expected {n} send and {n} recv tensors")
     nat = _native()
-    if nat.in_use():
+    if nat is not None and nat.in_use():
         rc = nat.call(nat.run_noalloc, ctypes.addressof(d), send, recv, n, send_n, recv_n,
                       int(d.dtype == AR_BFLOAT16), nat.stream(stream))
         if rc >= 0:

@@ -77,7 +77,7 @@ def start_tensor_args() -> subprocess.Popen:
     import torch
 
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DAR_TORCH_VERSION="{torch.__version__}"',
            "-I", sysconfig.get_paths()["include"],
            *[a for d in cpp_extension.include_paths() for a in ("-I", d)], TENSOR_ARGS_SRC,
            *[a for d in cpp_extension.library_paths() for a in ("-L", d)], "-ltorch_python", "-ltorch_cpu", "-lc10",

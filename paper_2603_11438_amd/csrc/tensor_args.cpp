@@ -99,4 +99,14 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tensor_args", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__tensor_args(void) { return PyModule_Create(&module); }
+// torch_version: the torch whose headers this was compiled with.  The binding
+// uses the module with that one alone.
+PyMODINIT_FUNC PyInit__tensor_args(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", AR_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
