@@ -1,6 +1,7 @@
 """The native call path of the Python binding (csrc/tensor_args.cpp): what it
 accepts runs and gives the oracle's bits, what it leaves to the checks in
-Python is accepted or refused as those checks always did."""
+Python is accepted or refused as those checks always did.  The same without
+the native part, where every call takes those checks and ctypes."""
 from __future__ import annotations
 
 import numpy as np
@@ -24,8 +25,18 @@ def ar():
     return ar
 
 
+@pytest.fixture(params=("native", "python"))
+def path(ar, request, monkeypatch):
+    """The binding's call path: native (which has to be there), or without it."""
+    if request.param == "native":
+        assert ar._native() is not None
+    else:
+        monkeypatch.setattr(ar, "_native_path", False)
+    return request.param
+
+
 @pytest.mark.parametrize("dtype", ("f32", "bf16"))
-def test_accepted_forms(ar, dtype):
+def test_accepted_forms(ar, path, dtype):
     """Lists and tuples of tensors, parameters, views with an offset, a
     stacked tensor (iterated), a subclass, and a stream of the caller's."""
     import torch
@@ -49,26 +60,34 @@ def test_accepted_forms(ar, dtype):
     with ar.Plan(n, count, dtype) as plan:
         for name, make in forms.items():
             send = make(to_device(x, dtype))
-            recv = make([torch.zeros(count, dtype=t.dtype, device="cuda:0") for t in send])
-            plan.run_oop(send, recv)
-            torch.cuda.synchronize()
-            assert_ranks_equal(list(recv), want, dtype, name)
-            ar.run_noalloc(list(send), list(recv), algo="ring")
+            def nans():
+                return make([torch.full((count,), float("nan"), dtype=t.dtype, device="cuda:0") for t in send])
+            calls = {"run_oop": lambda r: plan.run_oop(send, r), "bind": lambda r: plan.bind(send, r)(),
+                     "run_noalloc": lambda r: ar.run_noalloc(send if name in ("list", "tuple") else list(send),
+                                                             list(r), algo="ring")}
+            for what, run in calls.items():
+                recv = nans()
+                run(recv)
+                torch.cuda.synchronize()
+                assert_ranks_equal(list(recv), want, dtype, f"{name} {what}")
             plan.run(send)
             torch.cuda.synchronize()
             assert_ranks_equal(list(send), want, dtype, name + " in place")
         side = torch.cuda.Stream()
         send = to_device(x, dtype)
-        recv = [torch.zeros(count, dtype=t.dtype, device="cuda:0") for t in send]
+        with torch.cuda.stream(side):
+            current, given = ([torch.full((count,), float("nan"), dtype=t.dtype, device="cuda:0") for t in send]
+                              for _ in range(2))
         torch.cuda.synchronize()
         with torch.cuda.stream(side):
-            plan.run_oop(send, recv)          # the current stream
-            plan.run_oop(send, recv, side)
+            plan.run_oop(send, current)       # the current stream
+        plan.run_oop(send, given, side)       # a stream that is not the current one
         side.synchronize()
-        assert_ranks_equal(recv, want, dtype, "stream")
+        assert_ranks_equal(current, want, dtype, "current stream")
+        assert_ranks_equal(given, want, dtype, "given stream")
 
 
-def test_refused_forms(ar):
+def test_refused_forms(ar, path):
     import torch
 
     n, count = 4, 64

@@ -86,9 +86,8 @@ def test_blocks_against_links_in_memory(ar, coll, n):
 @pytest.mark.parametrize("dtype", ("f32", "bf16"))
 @pytest.mark.parametrize("n", (2, 3, 5, 8))
 def test_rings_of_a_plan(ar, n, dtype):
-    """The number of rings follows channels and waves, is a multiple of 256
-    beyond it, and is bounded by the compute units: messages of more pieces
-    than any of these, with the last ones partial."""
+    """Result bits of plans whose channels and waves give few and many rings,
+    with more pieces than rings, the last ones partial."""
     a = 4 if dtype == "f32" else 8
     count = n * (2100 if n == 2 else 1030) * _piece_units(n) * a - 7
     x = draw(n, count, dtype, "normal", seed=40 + n)
