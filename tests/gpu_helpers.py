@@ -52,6 +52,14 @@ def assert_ranks_equal(ts, want: np.ndarray, dtype: str, label: str = ""):
                                  f"got {got[i]:#x} want {want[i]:#x}")
 
 
+def assert_links(ar, plan):
+    """A ring's links are in device memory exactly where the plan asks for it
+    (FIFO-only, debug flags): a test of links in memory runs those."""
+    i = plan.info
+    in_memory = i["algo"] == ar.AR_ALGO_RING and i["grid"] > 0 and (not i["peer_direct"] or plan.desc.debug_flags != 0)
+    assert (plan.workspace_bytes > 0) == in_memory, (plan.workspace_bytes, i)
+
+
 def run_case(ar, x: np.ndarray, dtype: str, label: str = "", poison: bool = False, **plan_kw):
     """Run one AllReduce of x (N, count) and assert every rank equals the oracle."""
     import torch
@@ -62,6 +70,7 @@ def run_case(ar, x: np.ndarray, dtype: str, label: str = "", poison: bool = Fals
     want = oracle_bits(x, dtype)
     plan = ar.Plan(n, count, dtype, **plan_kw)
     try:
+        assert_links(ar, plan)
         if poison:
             plan.poison()
         plan.run(ts)

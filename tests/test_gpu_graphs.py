@@ -1,8 +1,9 @@
 """HIP-graph capture and replay of the collectives, checked against eager
 runs and the oracle on every replay.
 
-The ring keeps its message epoch in device memory, so a captured launch
-continues the flag counters of the runs before it.  Each replay here gets
+A ring with its links in memory (FIFO_ONLY: flags=2) keeps its message epoch
+there, so a captured launch continues the flag counters of the runs before
+it; one with its links in LDS keeps nothing.  Each replay here gets
 fresh input values (copied into the captured send buffers), so a replay
 that read stale FIFO contents or stale counters would produce the previous
 input's sums and fail.  Eager runs and synchronisations sit between the
@@ -13,12 +14,14 @@ import numpy as np
 import pytest
 
 from oracle import ring_oracle as ro
-from tests.gpu_helpers import assert_ranks_equal, draw, oracle_bits, say, to_bits, to_device
+from tests.gpu_helpers import assert_links, assert_ranks_equal, draw, oracle_bits, say, to_bits, to_device
 
 pytestmark = pytest.mark.gpu
 
 CFGS = [dict(proto="simple", nchannels=2), dict(proto="ll", nchannels=2), dict(proto="ll128", nchannels=2),
         dict(proto="simple", nchannels=1, chunk_bytes=1024, fifo_depth=2), dict(algo="direct")]
+FIFO_ONLY = 2  # links in memory
+CFGS += [dict(c, flags=FIFO_ONLY) for c in CFGS[:4]]
 
 
 @pytest.fixture(scope="module")
@@ -67,6 +70,7 @@ def _graph_case(ar, coll, dtype, cfg, n, count, runs_per_graph=3, replays=4):
     label = f"graph {coll} {dtype} N={n} count={count} {cfg}"
     say(label)
     plan = ar.Plan(n, count, dtype, coll=coll, **cfg)
+    assert_links(ar, plan)
     x0 = draw(n, ns, dtype, "normal", seed=500 + count)
     send = to_device(x0, dtype)
     recv = [torch.full((nr,), float("nan"), device="cuda:0").to(send[0].dtype) for _ in range(n)]
@@ -120,19 +124,22 @@ def test_graph_replay_allreduce(ar, cfg):
 
 
 @pytest.mark.parametrize("coll", ("reducescatter", "allgather"))
-@pytest.mark.parametrize("cfg", CFGS[:2] + CFGS[4:], ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+@pytest.mark.parametrize("cfg", CFGS[:2] + CFGS[4:8], ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
 def test_graph_replay_reduce_scatter_all_gather(ar, coll, cfg):
     _graph_case(ar, coll, "f32", cfg, 8, 1024)
 
 
-def test_epoch_continues_across_many_runs(ar):
-    """More LL messages than FIFO slots across eager runs, replays and a
-    second plan sharing nothing: the device-side epoch keeps every run's
-    flags distinct from the stale lines left in the slots."""
+@pytest.mark.parametrize("flags", (0, FIFO_ONLY))
+@pytest.mark.parametrize("proto", ("ll", "ll128", "simple"))
+def test_epoch_continues_across_many_runs(ar, proto, flags):
+    """More messages than FIFO slots across many runs: with links in memory
+    the device-side epoch keeps every run's flags distinct from the stale
+    lines left in the slots."""
     import torch
 
     n, count = 4, 64
-    plan = ar.Plan(n, count, "f32", proto="ll", nchannels=1, nwaves=1, fifo_depth=2)
+    plan = ar.Plan(n, count, "f32", proto=proto, nchannels=1, nwaves=1, fifo_depth=2, flags=flags)
+    assert_links(ar, plan)
     x = draw(n, count, "f32", "normal", seed=77)
     want = ro.allreduce_f32(x).view(np.uint32)
     send = to_device(x, "f32")
@@ -146,12 +153,13 @@ def test_epoch_continues_across_many_runs(ar):
     plan.destroy()
 
 
-def test_ring_plans_on_several_streams(ar):
+@pytest.mark.parametrize("flags", (0, FIFO_ONLY))
+def test_ring_plans_on_several_streams(ar, flags):
     """Ring plans of different protocols launched alternately on three
     streams (each grid small enough that all fit at once, so nothing here
     depends on the ordering to finish), with the direct algorithm on a
-    fourth: the library orders the ring launches across streams, and every
-    result matches the oracle."""
+    fourth: the library orders the launches of rings with links in memory
+    across streams, and every result matches the oracle."""
     import torch
 
     n = 8
@@ -162,7 +170,8 @@ def test_ring_plans_on_several_streams(ar):
     for i, (count, cfg) in enumerate(specs):
         x = draw(n, count, "f32", "uniform", seed=60 + i)
         xs.append(x)
-        plans.append(ar.Plan(n, count, "f32", **cfg))
+        plans.append(ar.Plan(n, count, "f32", flags=flags, **cfg))
+        assert_links(ar, plans[-1])
         sends.append(to_device(x, "f32"))
     torch.cuda.synchronize()
     for rep in range(12):
@@ -181,11 +190,13 @@ def test_ring_plans_on_several_streams(ar):
         p.destroy()
 
 
-def test_ring_plans_from_two_host_threads(ar):
+@pytest.mark.parametrize("flags", (0, FIFO_ONLY))
+def test_ring_plans_from_two_host_threads(ar, flags):
     """Two host threads, each with its own ring plan and stream, launch 40
-    runs each at the same time (the C calls run concurrently: ctypes
-    releases the interpreter lock).  The launch gate's per-device lock and
-    event keep the sequence consistent; every run's result is checked."""
+    runs each at the same time (the C calls run concurrently: they release
+    the interpreter lock).  With links in memory the launch gate's per-device
+    lock and event keep the sequence consistent; every run's result is
+    checked."""
     import threading
 
     import torch
@@ -199,7 +210,8 @@ def test_ring_plans_from_two_host_threads(ar):
             torch.cuda.set_device(0)
             x = draw(n, count, "f32", "uniform", seed=90 + i)
             send = to_device(x, "f32")
-            plan = ar.Plan(n, count, "f32", **cfg)
+            plan = ar.Plan(n, count, "f32", flags=flags, **cfg)
+            assert_links(ar, plan)
             stream = torch.cuda.Stream()
             fn_recv = [[torch.empty_like(t) for t in send] for _ in range(40)]
             with torch.cuda.stream(stream):

@@ -8,7 +8,7 @@ from __future__ import annotations
 
 import pytest
 
-from tests.gpu_helpers import say
+from tests.gpu_helpers import assert_links, say
 
 pytestmark = pytest.mark.gpu
 
@@ -54,8 +54,9 @@ def _check(t, label, offset=0):
             raise AssertionError(f"{label}: element {bad} is {float(t[bad])}, want {float(want[bad - lo])}")
 
 
-@pytest.mark.parametrize("cfg", [dict(algo="direct"), dict(proto="simple", nchannels=32)],
-                         ids=["direct", "ring-simple"])
+@pytest.mark.parametrize("cfg", [dict(algo="direct"), dict(proto="simple", nchannels=32),
+                                 dict(proto="simple", nchannels=32, flags=2)],
+                         ids=["direct", "ring-simple", "ring-simple-fifo"])
 def test_allreduce_segment_beyond_4gib(ar, cfg):
     import torch
 
@@ -67,6 +68,7 @@ def test_allreduce_segment_beyond_4gib(ar, cfg):
     _fill(bufs[1], P1, 2)
     torch.cuda.synchronize()
     plan = ar.Plan(n, count, "f32", **cfg)
+    assert_links(ar, plan)
     assert plan.info["seg_elems"] * 4 > (1 << 32)
     plan.run(bufs)
     torch.cuda.synchronize()

@@ -11,7 +11,7 @@ import pytest
 
 import workloads
 from oracle import ring_oracle as ro
-from tests.gpu_helpers import assert_ranks_equal, draw, oracle_bits, run_case, say, to_bits, to_device
+from tests.gpu_helpers import assert_links, assert_ranks_equal, draw, oracle_bits, run_case, say, to_bits, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -82,9 +82,10 @@ def test_ll128_line_tails(ar):
                              nwaves=1, flags=flags)
 
 
-def test_ll128_ordered_reads(ar):
-    """AR_PLAN_LL128_ORDERED: every batch is read after its flags were seen
-    current.  Same bits as the oracle for both dtypes, several rank counts,
+@pytest.mark.parametrize("links", ("lds", "memory"))
+def test_ll128_ordered_reads(ar, links):
+    """AR_PLAN_LL128_ORDERED, with links in memory (FIFO-only): every batch is
+    read after its flags were seen current.  Links in LDS ignore the flag.  Same bits as the oracle for both dtypes, several rank counts,
     ragged counts, one and three channels, and both batch widths (one wave
     per rank, so segments of 60+ elements run four-access batches)."""
     for dtype in ("f32", "bf16"):
@@ -93,7 +94,8 @@ def test_ll128_ordered_reads(ar):
                 x = draw(n, count, dtype, "normal", seed=3100 + 7 * n + count)
                 for nch, nw in ((1, 1), (3, 4)):
                     run_case(ar, x, dtype, f"ll128-ordered-{dtype}-{n}-{count}-{nch}-{nw}", proto="ll128",
-                             nchannels=nch, nwaves=nw, flags=ar.AR_PLAN_LL128_ORDERED)
+                             nchannels=nch, nwaves=nw,
+                             flags=ar.AR_PLAN_LL128_ORDERED | (ar.AR_PLAN_FIFO_ONLY if links == "memory" else 0))
 
 
 def test_bound_calls(ar):
@@ -358,8 +360,9 @@ def test_fp64_normwise_bound_full_size(ar):
 
 # ------------------------------------------------ in place, repeats, epochs
 
+@pytest.mark.parametrize("flags", (0, 2), ids=("lds", "fifo"))
 @pytest.mark.parametrize("proto", PROTOS)
-def test_out_of_place_equals_in_place(ar, proto):
+def test_out_of_place_equals_in_place(ar, proto, flags):
     import torch
 
     n, count, dtype = 8, 100003, "f32"
@@ -367,7 +370,8 @@ def test_out_of_place_equals_in_place(ar, proto):
     want = oracle_bits(x, dtype)
     send = to_device(x, dtype)
     recv = [torch.full_like(t, float("nan")) for t in send]
-    plan = ar.Plan(n, count, dtype, proto=proto, nchannels=4)
+    plan = ar.Plan(n, count, dtype, proto=proto, nchannels=4, flags=flags)
+    assert_links(ar, plan)
     plan.run_oop(send, recv)
     torch.cuda.synchronize()
     assert_ranks_equal(recv, want, dtype, "oop")
@@ -379,14 +383,16 @@ def test_out_of_place_equals_in_place(ar, proto):
 
 @pytest.mark.parametrize("proto", PROTOS)
 @pytest.mark.parametrize("dtype", ("f32", "bf16"))
-def test_repeated_runs_poisoned_fifo(ar, proto, dtype):
-    """Back-to-back runs of one plan with the FIFO poisoned (0xFF) before each
-    run: a reader that consumed a slot before its writer filled it would see
+@pytest.mark.parametrize("flags", (0, 2), ids=("lds", "fifo"))
+def test_repeated_runs_poisoned_fifo(ar, proto, dtype, flags):
+    """Back-to-back runs of one plan with the FIFO (of a FIFO-only plan; links
+    in LDS have none) poisoned (0xFF) before each run: a reader that consumed a slot before its writer filled it would see
     NaN.  Flag epochs advance across runs with no reset."""
     import torch
 
     n, count = 8, 40000
-    plan = ar.Plan(n, count, dtype, proto=proto, nchannels=3, fifo_depth=2)
+    plan = ar.Plan(n, count, dtype, proto=proto, nchannels=3, fifo_depth=2, flags=flags)
+    assert_links(ar, plan)
     for it in range(30):
         x = draw(n, count, dtype, "normal", seed=500 + it)
         ts = to_device(x, dtype)
@@ -406,7 +412,8 @@ def test_jitter_keeps_results(ar, proto):
                  debug_flags=ar.AR_DEBUG_JITTER)
 
 
-def test_many_runs_one_stream(ar):
+@pytest.mark.parametrize("flags", (0, 2), ids=("lds", "fifo"))
+def test_many_runs_one_stream(ar, flags):
     """Many runs queued on one stream without synchronising in between."""
     import torch
 
@@ -415,7 +422,8 @@ def test_many_runs_one_stream(ar):
     base = to_device(x, "f32")
     want = oracle_bits(x, "f32")
     for proto in PROTOS:
-        plan = ar.Plan(n, count, "f32", proto=proto, nchannels=8)
+        plan = ar.Plan(n, count, "f32", proto=proto, nchannels=8, flags=flags)
+        assert_links(ar, plan)
         outs = []
         for _ in range(200):
             ts = [t.clone() for t in base]

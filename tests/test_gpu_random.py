@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from oracle import ring_oracle as ro
-from tests.gpu_helpers import draw, say, to_bits, to_device
+from tests.gpu_helpers import assert_links, draw, say, to_bits, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -34,8 +34,8 @@ def _case(rng):
         cfg["chunk_bytes"] = int(rng.choice([16, 256, 1024, 4096, 65536]))
         cfg["fifo_depth"] = int(rng.choice([2, 3, 4, 8]))
         cfg["placement"] = int(rng.integers(0, 2))
-        # 2: Simple all-gather through the FIFOs; 4: LL128 reads lines only
-        # after their flags
+        # 2: links in memory (FIFO-only); 4: LL128 reads lines only after their
+        # flags (which links in LDS ignore)
         cfg["flags"] = int(rng.choice([0, 2, 4]))
     else:
         cfg["nchannels"] = int(rng.choice([0, 1, 3, 16]))
@@ -108,20 +108,40 @@ def ar():
     return ar
 
 
+def _random_case(ar, block, i, case):
+    coll, dtype, n, count, cfg, in_place = case
+    label = f"random block {block} case {i}: {coll} {dtype} N={n} count={count} {cfg} in_place={in_place}"
+    say(label)
+    plan = ar.Plan(n, count, dtype, coll=coll, **cfg)
+    try:
+        assert_links(ar, plan)
+        for rep in range(2):
+            elems = n * count if coll == "reducescatter" else count
+            x = draw(n, elems, dtype, "normal", seed=1000 * block + 10 * i + rep)
+            got = _run(ar, plan, coll, x, dtype, n, count, in_place)
+            assert plan.status() == ar.AR_OK, f"{label}: status"
+            assert np.array_equal(got, _expected(coll, x, dtype, n)), f"{label}: run {rep}"
+    finally:
+        plan.destroy()
+
+
 @pytest.mark.parametrize("block", range(4))
 def test_random_plans(ar, block):
     rng = np.random.default_rng(20260 + block)
     for i in range(NCASES // 4):
+        _random_case(ar, block, i, _case(rng))
+
+
+@pytest.mark.parametrize("block", range(4, 6))
+def test_random_rings_with_links_in_memory(ar, block):
+    """The same draws as FIFO-only rings, every other one with ordered LL128
+    reads too."""
+    rng = np.random.default_rng(20260 + block)
+    done = 0
+    while done < NCASES // 4:
         coll, dtype, n, count, cfg, in_place = _case(rng)
-        label = f"random block {block} case {i}: {coll} {dtype} N={n} count={count} {cfg} in_place={in_place}"
-        say(label)
-        plan = ar.Plan(n, count, dtype, coll=coll, **cfg)
-        try:
-            for rep in range(2):
-                elems = n * count if coll == "reducescatter" else count
-                x = draw(n, elems, dtype, "normal", seed=1000 * block + 10 * i + rep)
-                got = _run(ar, plan, coll, x, dtype, n, count, in_place)
-                assert plan.status() == ar.AR_OK, f"{label}: status"
-                assert np.array_equal(got, _expected(coll, x, dtype, n)), f"{label}: run {rep}"
-        finally:
-            plan.destroy()
+        if cfg["algo"] != "ring":
+            continue
+        cfg["flags"] = ar.AR_PLAN_FIFO_ONLY | (ar.AR_PLAN_LL128_ORDERED if done % 2 else 0)
+        _random_case(ar, block, done, (coll, dtype, n, count, cfg, in_place))
+        done += 1

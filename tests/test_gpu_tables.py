@@ -4,9 +4,9 @@ The fp32 AllReduce rows are covered by the D4 sweep in test_gpu_parity.py.
 Here: the bf16 AllReduce table, and the ReduceScatter and AllGather tables
 of both data types, at every power-of-two size from 4 KiB to 128 MiB
 (AllReduce: bytes per rank; ReduceScatter and AllGather: bytes of one
-rank's full buffer).  Each size runs the table's overall choice and its
-ring choice (protocol, channels, chunk and waves for that size), out of
-place, and compares every rank's output with the CPU oracle bit for bit.
+rank's full buffer).  Each size runs the table's overall choice, its ring
+choice, and that choice with its links in memory (FIFO-only: the row's
+protocol, channels, chunk and waves as such), out of place, and compares every rank's output with the CPU oracle bit for bit.
 """
 from __future__ import annotations
 
@@ -15,13 +15,13 @@ import pytest
 
 import workloads
 from oracle import ring_oracle as ro
-from tests.gpu_helpers import say, to_device
+from tests.gpu_helpers import assert_links, say, to_device
 
 pytestmark = pytest.mark.gpu
 
 N = 8
 SIZES = workloads.WORKLOADS["D4"].extra["sizes"]
-CFGS = (dict(proto="auto"), dict(proto="auto", algo="ring"))
+CFGS = (dict(proto="auto"), dict(proto="auto", algo="ring"), dict(proto="auto", algo="ring", flags=2))
 ELEM = {"f32": 4, "bf16": 2}
 
 
@@ -66,6 +66,7 @@ def _run(ar, coll, count, dtype, cfg, send, recv_elems):
     recv = [torch.empty(recv_elems, dtype=send[0].dtype, device="cuda:0") for _ in range(N)]
     plan = ar.Plan(N, count, dtype, coll=coll, **cfg)
     try:
+        assert_links(ar, plan)
         plan.run_oop(send, recv)
         torch.cuda.synchronize()
         assert plan.status() == ar.AR_OK, (coll, count, dtype, cfg)

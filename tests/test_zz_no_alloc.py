@@ -1,15 +1,16 @@
 """The allocation-free entry point (ar_run_noalloc) against the plan-based one
 (ar_plan_ex + ar_run_oop), through the C ABI, bit for bit, and both against
-the CPU oracle.  Each case calls the allocation-free entry twice in a row on
-the same device scratch, the second time with a smaller input, so the second
-call must clear what the first one left there."""
+the CPU oracle.  Each case calls the allocation-free entry twice in a row, the
+second time with a smaller input; where the links are in memory (FIFO-only:
+flags=2, LL128 also with ordered reads: 6) both calls use the same device
+scratch, so the second one must clear what the first one left there."""
 from __future__ import annotations
 
 import numpy as np
 import pytest
 
 from oracle import ring_oracle as ro
-from tests.gpu_helpers import draw, say, to_bits, to_device
+from tests.gpu_helpers import assert_links, draw, say, to_bits, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -58,6 +59,7 @@ def _one(ar, n, count, dtype, coll, cfg, seed):
     torch.cuda.synchronize()
     plan = ar.Plan(n, count, dtype, coll=coll, **cfg)
     try:
+        assert_links(ar, plan)
         plan.run_oop(send, recv_b)
         torch.cuda.synchronize()
         assert plan.status() == ar.AR_OK
@@ -86,6 +88,16 @@ CASES = [
     ("reducescatter", "bf16", dict(proto="simple", nchannels=2)),
     ("allgather", "f32", dict(proto="ll128", nchannels=2)),
     ("allgather", "bf16", dict(proto="simple", nchannels=3)),
+    ("allreduce", "f32", dict(proto="ll", nchannels=2, flags=2)),
+    ("allreduce", "f32", dict(proto="ll128", nchannels=2, flags=2)),
+    ("allreduce", "f32", dict(proto="ll128", nchannels=2, flags=6)),
+    ("allreduce", "bf16", dict(proto="simple", nchannels=5, flags=2)),
+    ("allreduce", "bf16", dict(proto="ll", nchannels=3, flags=2)),
+    ("allreduce", "bf16", dict(proto="ll128", nchannels=1, flags=2)),
+    ("reducescatter", "f32", dict(proto="ll", nchannels=2, flags=2)),
+    ("reducescatter", "bf16", dict(proto="simple", nchannels=2, flags=2)),
+    ("allgather", "f32", dict(proto="ll128", nchannels=2, flags=2)),
+    ("allgather", "bf16", dict(proto="simple", nchannels=3, flags=2)),
 ]
 
 
@@ -99,7 +111,8 @@ def test_noalloc_matches_plan_twice(ar, coll, dtype, cfg):
             assert info["fifo_bytes"] + info["flag_bytes"] <= ar.AR_NOALLOC_SCRATCH_BYTES
 
 
-def test_noalloc_in_place_and_ranks(ar):
+@pytest.mark.parametrize("flags", (0, 2), ids=("lds", "fifo"))
+def test_noalloc_in_place_and_ranks(ar, flags):
     """In place, N from 1 to 16, ragged counts, on the scratch left by the
     cases before."""
     import torch
@@ -109,7 +122,7 @@ def test_noalloc_in_place_and_ranks(ar):
         x = draw(n, count, "f32", "uniform", seed=31 * n + count)
         ts = to_device(x, "f32")
         say(f"noalloc in place N={n} count={count} {proto}")
-        ar.run_noalloc(ts, proto=proto, nchannels=2)
+        ar.run_noalloc(ts, proto=proto, nchannels=2, flags=flags)
         torch.cuda.synchronize()
         want = ro.allreduce(x, "f32").view(np.uint32)
         for t in ts:
@@ -137,15 +150,17 @@ def test_noalloc_rejects_what_it_cannot_hold(ar):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("flags", (0, 2), ids=("lds", "fifo"))
 @pytest.mark.parametrize("cfg", [dict(proto="ll", nchannels=2), dict(proto="simple", nchannels=3),
                                  dict(proto="ll128", nchannels=2)], ids=lambda c: c["proto"])
-def test_noalloc_graph_replay(ar, cfg):
-    """Calls captured into a HIP graph: each replay clears the scratch with
-    the captured fill kernel and runs the ring from message 0 again, so
+def test_noalloc_graph_replay(ar, cfg, flags):
+    """Calls captured into a HIP graph: with links in memory each replay clears
+    the scratch with the captured fill kernel and runs the ring from message 0 again, so
     every replay, on fresh input values, gives the oracle's bits; eager
     calls with other values run between the replays."""
     import torch
 
+    cfg = dict(cfg, flags=flags)
     n, count = 8, 4099
     x0 = draw(n, count, "f32", "normal", seed=810)
     send = to_device(x0, "f32")
