@@ -535,15 +535,38 @@ int ar_reload_tuner(ar_tuner_fn fn, void *user, ar_reload_stats *stats)
     return install(fn, user, true, stats);
 }
 
-// What a row's direct columns become where the rank count has a kernel of
-// another shape than the eight ranks they were measured with.  Only for the
-// library's own use of its table: a caller's tuner is taken at its word.
+// What a row's direct columns become at another rank count than the eight
+// they were measured with.  Only for the library's own use of its table: a
+// caller's tuner is taken at its word.
 static void fit_direct_to_ranks(const ar_tune_ctx &c, ar_tune_out *out)
 {
     const uint64_t e = c.dtype == AR_FLOAT32 ? 4 : 2, n = (uint64_t)c.nranks;
     const uint64_t units = ceil_div(ceil_div(c.msg_bytes / e, n), 16 / e);  // 16-byte units of a segment
+    const bool large = c.msg_bytes > (8u << 20);  // a thread has several iterations
+    if (large && c.coll != AR_COLL_ALLGATHER && n > 4 && n % 4 != 0) {
+        // A sum over ranks that are no multiple of four: a segment's workgroups fall on
+        // all XCDs in turn, and the rows' few long-lived workgroups come out
+        // uneven (their scaled grids end a little above 256, see below).
+        // About 1024 workgroups even that out, of four waves and one unit per
+        // thread, or, for AllReduce beyond 64 MiB, of one wave and two units
+        // (row's geometry / four waves / one wave, AllReduce: 6 ranks, fp32,
+        // 48 MiB 152 / 112 / 111 us, 128 MiB 448 / 333 / 321; 7 ranks, fp32,
+        // 12 MiB 47 / 35 / 36, 128 MiB 559 / 417 / 392, bf16, 128 MiB 393 /
+        // 418 / 388; ReduceScatter bf16, 7 ranks, 96 MiB 200 / 151).
+        const bool one = c.coll == AR_COLL_ALLREDUCE && n < 8 && c.msg_bytes > (64u << 20);
+        out->direct_parts = (int)(1024 / n);
+        out->direct_nwaves = one ? 1 : 4;
+        out->direct_unroll = one ? 2 : 1;
+        return;
+    }
+    // A grid that ends a little above a multiple of the 256 compute units
+    // would take a whole round more: one workgroup per segment fewer
+    // (AllGather, 7 ranks, 128 MiB bf16: 259 workgroups 259 us, 252 212 us; 6
+    // ranks, 48 MiB: 258 79 us, 252 66 us).
+    const uint64_t over = (uint64_t)out->direct_parts * n % 256;
+    if (large && out->direct_parts > 1 && over > 0 && over < n) --out->direct_parts;
     const uint64_t parts = (uint64_t)out->direct_parts;
-    if (c.nranks > 8 && out->direct_unroll == 2) {
+    if (n > 8 && out->direct_unroll == 2) {
         // The kernels of 9..16 ranks have one unit per thread; four times the
         // workgroups, as far as there is a unit for each, stand for the second
         // (16 ranks, 48 MiB, AllReduce: 320-334 us with as many or twice, 305
@@ -554,7 +577,7 @@ static void fit_direct_to_ranks(const ar_tune_ctx &c, ar_tune_out *out)
     // Two ranks' AllGather has one load and two stores per unit, the least
     // in flight of all: twice the waves (20 MiB: 14.4 against 12.6 us, 48 MiB:
     // 30.5 against 27 us), unless the workgroups already outnumber the units.
-    if (c.coll == AR_COLL_ALLGATHER && c.nranks == 2 && out->direct_nwaves <= AR_MAX_WAVES / 2 && parts < units)
+    if (c.coll == AR_COLL_ALLGATHER && n == 2 && out->direct_nwaves <= AR_MAX_WAVES / 2 && parts < units)
         out->direct_nwaves *= 2;
 }
 

@@ -30,15 +30,18 @@ def test_a_tuners_answer_is_kept(parts, waves, n, coll, count, unroll):
 
 @pytest.mark.parametrize("dtype", ("f32", "bf16"))
 @pytest.mark.parametrize("coll", ("allreduce", "reducescatter", "allgather"))
-@pytest.mark.parametrize("n", (2, 3, 9, 11, 16))
+@pytest.mark.parametrize("n", range(2, 17))
 def test_table_rows_at_other_rank_counts(n, coll, dtype):
-    """A row's workgroups keep the grid of eight ranks; more than eight ranks
-    take four times as many where the row has two units per thread, as far as
-    there is a unit for each, and a two-rank AllGather twice the waves."""
+    """A row's workgroups keep the grid of eight ranks, beyond 8 MiB never a
+    little above a multiple of 256; more than eight ranks take four times as
+    many where the row has two units per thread, as far as there is a unit for
+    each; a two-rank AllGather takes twice the waves; and sums over more
+    than four ranks that are no multiple of four take 1024 workgroups beyond 8
+    MiB."""
     ar.lib()
     c = ar.COLLS[coll]
     a = 4 if dtype == "f32" else 8
-    doubled = quadrupled = 0
+    odd = coll != "allgather" and n in (5, 6, 7, 9, 10, 11, 13, 14, 15)
     for lg in range(8, 28):
         for size in (1 << lg, (3 << lg) // 2 // (16 * n) * 16 * n):
             row = ar.ar_tuner_raw("table", size, 8, dtype, coll=c)
@@ -47,12 +50,17 @@ def test_table_rows_at_other_rank_counts(n, coll, dtype):
             parts, waves, unroll = row["direct_parts"], row["direct_nwaves"], row["direct_unroll"]
             if parts:
                 parts = max(1, (parts * 8 + n // 2) // n)
-            if coll == "allgather" and n == 2 and parts < units:
-                waves, doubled = 2 * waves, doubled + 1
-            if n > 8 and unroll == 2:
-                parts, unroll, quadrupled = max(parts, min(4 * parts, units)), 1, quadrupled + (parts > 0)
+                if size > 8 << 20:
+                    parts -= parts > 1 and 0 < parts * n % 256 < n
+                    assert not (parts > 1 and 0 < parts * n % 256 < n)
+            if odd and size > 8 << 20:
+                one = coll == "allreduce" and n < 8 and size > 64 << 20
+                parts, waves, unroll = 1024 // n, 1 if one else 4, 2 if one else 1
+            elif n > 8 and unroll == 2:
+                parts, unroll = max(parts, min(4 * parts, units)), 1
+            elif coll == "allgather" and n == 2 and parts < units:
+                waves *= 2
             assert (got["direct_parts"], got["direct_nwaves"], got["direct_unroll"]) == (parts, waves, unroll), size
-    assert (doubled > 0) == (coll == "allgather" and n == 2) and (quadrupled > 0) == (n > 8)
 
 
 @pytest.mark.parametrize("n,count,waves", [(8, 1001, 16), (8, 1001, 4), (16, 16 * 4 * 1000, 4), (16, 1 << 39, 9),
