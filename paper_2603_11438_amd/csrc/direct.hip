@@ -167,7 +167,14 @@ __global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs
 
 typedef void (*DirectFn)(DirectArgs);
 
-// per_thread: 16-byte units of a segment per thread of its workgroups.
+// per_thread: 16-byte units of a segment per thread of its workgroups.  Where
+// half of a plan's units per iteration already hold an AllReduce's of three or
+// four ranks, the kernel with half: with more, half of the workgroups would
+// have nothing to do (AllReduce, 4 ranks, fp32, 64 workgroups of 8 waves per
+// segment, cold buffers: 3 MiB 8.8 us with four units, 6.4 with two; 4 MiB 8.9
+// and 7.2).  Elsewhere fewer workgroups with more loads each are as fast or
+// faster (2 ranks, 4 MiB bf16: 3.5 us with four units, 4.5 with two; 8 ranks,
+// 1.5 MiB fp32: 5.5 and 5.8; ReduceScatter, 2 ranks, 4 MiB: 2.5 and 2.8).
 template <int DT, int COLL, bool KEEP, int N = AR_MAX_RANKS>
 __host__ DirectFn direct_fn(int nranks, int unroll, uint64_t per_thread)
 {
@@ -175,8 +182,9 @@ __host__ DirectFn direct_fn(int nranks, int unroll, uint64_t per_thread)
         if (nranks != N) return direct_fn<DT, COLL, KEEP, N - 1>(nranks, unroll, per_thread);
         constexpr int U = units_per_unroll(N, COLL);
         if constexpr (N <= 8) {
-            if (unroll == 2) return per_thread > 2 * U ? direct_kernel<DT, N, COLL, 2 * U, true, KEEP>
-                                                         : direct_kernel<DT, N, COLL, 2 * U, false, KEEP>;
+            if (unroll == 2 && (per_thread > U || COLL != AR_COLL_ALLREDUCE || N < 3 || N > 4))
+                return per_thread > 2 * U ? direct_kernel<DT, N, COLL, 2 * U, true, KEEP>
+                                          : direct_kernel<DT, N, COLL, 2 * U, false, KEEP>;
         }
         return per_thread > U ? direct_kernel<DT, N, COLL, U, true, KEEP> : direct_kernel<DT, N, COLL, U, false, KEEP>;
     }
