@@ -151,8 +151,15 @@ __global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs
         const bool more = LOOP && next < n;
         // The next units' loads go out before these units' stores: loads
         // and stores retire in order, so loads issued after the stores could
-        // only be waited for together with them.
-        if (more) load(next);
+        // only be waited for together with them.  That is what eight ranks'
+        // pairs of fp32 units are better with once the outputs are streamed
+        // to HBM: sixteen loads, then sixteen stores (AllReduce, 32 workgroups
+        // of two waves per segment, mean of three buffer layouts, repeated and
+        // cold, loads first and stores first: 32 MiB 93.8 and 92.5 us, 64 MiB
+        // 185.8 and 183.2, 128 MiB 389 and 381; but bf16, 64 workgroups of one
+        // wave, 96 MiB 286 and 296).
+        constexpr bool kLoadsFirst = !(DT == AR_FLOAT32 && N == 8 && U == 2 && COLL == AR_COLL_ALLREDUCE && !KEEP);
+        if (kLoadsFirst && more) load(next);
 #pragma unroll
         for (int j = 0; j < NDST; ++j) {
             const Rsrc w = make_rsrc(dst_of(j) + off, b);
@@ -160,6 +167,7 @@ __global__ __launch_bounds__(64 * kMaxDirectWaves) void direct_kernel(DirectArgs
             for (int t = 0; t < U; ++t) st128<kOut>(w, (t * nth + tid) * 16, y[t]);
         }
         if (!more) return;
+        if (!kLoadsFirst) load(next);
         arrive();
         off = next;
     }
