@@ -212,9 +212,10 @@ typedef struct ar_plan_desc {
  *   AR_PLAN_FIFO_ONLY  ring plans: links in memory, every hop through the
  *                    FIFOs.  By default the links are in LDS: the plan's
  *                    nchannels * nranks workgroups of nwaves waves become up
- *                    to nchannels * nranks * nwaves / 2 rings of one
- *                    workgroup, and chunk_bytes, fifo_depth, placement and the
- *                    watchdog do not apply.  A plan with debug flags and
+ *                    to nchannels * nranks * nwaves / 2 rings (4 * nchannels
+ *                    * nwaves if that is more) of one workgroup of nranks
+ *                    waves, and proto, chunk_bytes, fifo_depth, placement and
+ *                    the watchdog do not apply.  A plan with debug flags and
  *                    without this one has links in memory in the peer-direct
  *                    mode: the second rank of each reduce-scatter chain
  *                    reads the chain start's input from that rank's buffer

@@ -94,6 +94,42 @@ constexpr uint64_t direct_max_parts(int nranks, int nwaves)
     return (0xFFFFFFFFull / direct_threads(nwaves) - 1) / (direct_split(nwaves) * (uint64_t)nranks);
 }
 
+// Workgroups (rings) of a ring plan with its links in LDS, for segments of
+// seg_b bytes in pieces of piece_b.
+//
+// The plan's C * N workgroups of W waves become C * N * W / 2 rings of N
+// waves, or 4 * C * W where those are more (below eight ranks), so that few
+// ranks get as many waves as eight.  Simple default, 16 channels of 4 waves:
+// 8 ranks, bf16, 9 MiB 37.9 us with C * N rings, 30.2 with C * N * W / 2; 2
+// ranks, fp32, 4 MiB 14.5 us with 64 rings, 6.3 with 256, 32 MiB 97 and 34
+// us; 4 ranks, 32 MiB, 128 and 256 rings 76 and 51 us.  The channel and wave
+// counts a caller names are thus a limit on the rings, of N waves each, not
+// on the waves themselves.
+//
+// Not more than fill the compute units twice (512 workgroups, more of few
+// ranks); where the inputs together exceed half of the 256 MiB last-level
+// cache, once: more only widen the stretch of memory that is open at a time (8
+// ranks, fp32, 256 against 512 workgroups: 128 MiB 385 and 400 us, 32 MiB 101
+// and 104 us), while a message that the cache holds gains from the second
+// workgroup per compute unit (8 MiB 24.8 and 23.9 us, 4 MiB 13.1 and 12.1 us).
+// Beyond 256 down to a multiple of 256, as many on each compute unit (bf16, 5
+// ranks, 16 MiB, 255 / 320 / 380 / 510 workgroups: 31.8 / 41.0 / 33.9 / 31.5
+// us; 7 ranks, 48 MiB, 252 and 292: 164 and 204 us); that takes 504 to 511,
+// which a table row of 32 channels comes to at 9 and 11 to 15 ranks, to 256
+// as well.  At last, not more than there are pieces, whatever that leaves.
+inline uint64_t ring_lds_workgroups(const ar_plan_info &g, uint64_t seg_b, uint64_t piece_b)
+{
+    const uint64_t n = (uint64_t)g.nranks, c = (uint64_t)g.nchannels, w = (uint64_t)g.nwaves;
+    const uint64_t pieces = (seg_b + piece_b - 1) / piece_b;
+    const uint64_t in_b = seg_b * n * (g.coll == AR_COLL_ALLGATHER ? 1 : n);
+    const uint64_t once = n == 2 ? 1024 : n < 5 ? 512 : 256, most = in_b > (128ull << 20) ? once : 2 * once;
+    uint64_t grid = c * n * ((w + 1) / 2);
+    if (grid < 4 * c * w) grid = 4 * c * w;
+    if (grid > most) grid = most;
+    if (grid > 256) grid -= grid % 256;
+    return grid > pieces ? pieces : grid;
+}
+
 // How the outputs of a run in LDS or of the direct algorithm are stored.  All
 // ranks' outputs together up to half of the 256 MiB last-level cache: written
 // through the L2 to the memory side (sc1), where that cache takes them, and

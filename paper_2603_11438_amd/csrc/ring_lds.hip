@@ -291,10 +291,6 @@ __host__ RingFn lds_fn_of(int coll, int nranks, uint32_t *piece)
 
 }  // namespace dev
 
-// Inputs of all ranks together above which a run streams from HBM: half of
-// the 256 MiB last-level cache.
-constexpr uint64_t kLargeInputBytes = 128ull << 20;
-
 int launch_ring_lds(const ar_plan_info &info, const RingArgs &args, void *stream)
 {
     uint32_t piece = 0;
@@ -303,30 +299,10 @@ int launch_ring_lds(const ar_plan_info &info, const RingArgs &args, void *stream
                           : (keep ? dev::lds_fn_of<AR_BFLOAT16, true> : dev::lds_fn_of<AR_BFLOAT16, false>);
     const dev::RingFn fn = pick(info.coll, info.nranks, &piece);
     if (!fn) return AR_ERR_UNSUPPORTED;
-    // The plan's C * N workgroups of W waves become C * N * W / 2 rings (the
-    // Simple default of 16 channels of 4 waves, 8 ranks, bf16, 9 MiB: 37.9 us
-    // with C * N rings, 30.2 with these).  Not more than there are pieces, and
-    // not more than fill the compute units twice (512 workgroups, more of few
-    // ranks); where the inputs together exceed half the last-level cache,
-    // once: more only widen the stretch of memory that is open at a time (8
-    // ranks, fp32, 256 against 512 workgroups: 128 MiB 385 and 400 us, 32 MiB
-    // 101 and 104 us), while a message that the cache holds gains from the
-    // second workgroup per compute unit (8 MiB 24.8 and 23.9 us, 4 MiB 13.1
-    // and 12.1 us).  Beyond 256 a multiple of 256, as many on each compute
-    // unit (bf16, 5 ranks, 16 MiB, 255 / 320 / 380 / 510 workgroups: 31.8 /
-    // 41.0 / 33.9 / 31.5 us; 7 ranks, 48 MiB, 252 and 292: 164 and 204 us; 3
-    // ranks, 48 MiB, 510 and 600: 56.2 and 61.7 us).
-    const uint64_t seg_b = args.seg * (f32 ? 4 : 2), n = (uint64_t)info.nranks;
-    const uint64_t pieces = (seg_b + piece - 1) / piece;
-    const uint64_t in_b = seg_b * n * (info.coll == AR_COLL_ALLGATHER ? 1 : n);
-    const uint64_t once = n == 2 ? 1024 : n < 5 ? 512 : 256, most = in_b > kLargeInputBytes ? once : 2 * once;
-    uint64_t grid = (uint64_t)info.nchannels * n * (((uint64_t)info.nwaves + 1) / 2);
-    if (grid > most) grid = most;
-    if (grid > 256) grid -= grid % 256;
-    if (grid > pieces) grid = pieces;
+    const uint64_t grid = ring_lds_workgroups(info, args.seg * (f32 ? 4 : 2), piece);
     RingArgs a = args;
     void *kargs[] = {&a};
-    return hipLaunchKernel((const void *)fn, dim3((unsigned)grid), dim3(64u * (unsigned)n), kargs, 0,
+    return hipLaunchKernel((const void *)fn, dim3((unsigned)grid), dim3(64u * (unsigned)info.nranks), kargs, 0,
                            (hipStream_t)stream) == hipSuccess ? AR_OK : AR_ERR_HIP;
 }
 

@@ -35,12 +35,13 @@ def _piece_units(n, coll="allreduce"):
 @pytest.mark.parametrize("n", range(2, 17))
 def test_allreduce_edges(ar, n, dtype):
     """Counts whose last segment ends inside, at and just past a piece, a lane
-    and a unit; one channel of one wave, so n rings share the pieces: one piece or fewer
-    per ring, and two and three with the next one loaded ahead."""
+    and a unit; one channel of one wave, so max(n, 4) rings share the pieces: one
+    piece or fewer per ring, and two and three with the next one loaded ahead."""
     a = 4 if dtype == "f32" else 8
     p = _piece_units(n) * a  # elements of a piece
-    counts = [1, a + 1, n * a, n * p - 1, n * p, n * p + 1, n * p + n * a - a + 1, n * (n + 1) * p + 3,
-              n * (2 * n + 1) * p - p - 5]
+    rings = max(n, 4)
+    counts = [1, a + 1, n * a, n * p - 1, n * p, n * p + 1, n * p + n * a - a + 1, n * (rings + 1) * p + 3,
+              n * (2 * rings + 1) * p - p - 5]
     for i, count in enumerate(counts):
         x = draw(n, count, dtype, "normal", seed=900 + 31 * n + i)
         proto = ("simple", "ll", "ll128")[i % 3]
@@ -57,7 +58,7 @@ def test_blocks_against_links_in_memory(ar, coll, n):
     for dtype in ("f32", "bf16"):
         a = 4 if dtype == "f32" else 8
         p = _piece_units(n, coll) * a
-        for count in (a, p - a, p + a, (2 * n + 1) * p + 3 * a):
+        for count in (a, p - a, p + a, (2 * max(n, 4) + 1) * p + 3 * a):
             ns, nr = (n * count, count) if coll == "reducescatter" else (count, n * count)
             x = draw(n, ns, dtype, "normal", seed=count + n)
             want = ro.reduce_scatter(x, dtype) if coll == "reducescatter" else np.stack([ro.all_gather(x)] * n)
