@@ -97,8 +97,8 @@ enum { AR_PROTO_AUTO = -1, AR_PROTO_LL = 0, AR_PROTO_LL128 = 1, AR_PROTO_SIMPLE 
  * or tree, besides protocol and channels).
  *   AR_ALGO_AUTO    no preference: a requested protocol implies the ring,
  *                   otherwise the tuner decides (no opinion = ring)
- *   AR_ALGO_RING    reduce-scatter + all-gather around the ring, through
- *                   FIFOs, under a protocol and channel count
+ *   AR_ALGO_RING    reduce-scatter + all-gather around the ring, over links
+ *                   in LDS or, on request, through FIFOs under a protocol
  *   AR_ALGO_DIRECT  two-shot direct reduce: for each segment, one group of
  *                   workgroups reads that segment of every rank buffer
  *                   directly, sums it in the same chain order as the ring
@@ -165,9 +165,13 @@ enum {
  *   AR_DEBUG_TRACE      channel 0 / wave 0 of every rank writes one record
  *                       per ring step into the buffer given by
  *                       ar_plan_debug_trace (see there).
- * A ring plan with any debug flag runs a kernel build that carries these
- * hooks; plans without them run one that does not (the hooks cost time even
- * when not taken). */
+ * A ring plan with any debug flag has its links in memory and runs a kernel
+ * build that carries these hooks; plans without them run one that does not
+ * (the hooks cost time even when not taken).  The hooks belong to lines and
+ * counters in memory: what they show holds for FIFO-only plans, whose kernels
+ * are the same but for them (ask for both: a debug plan without
+ * AR_PLAN_FIFO_ONLY runs the peer-direct mode, which no other plan does),
+ * and says nothing about a default plan, whose links are in LDS. */
 enum { AR_DEBUG_SKIP_POST = 1u, AR_DEBUG_JITTER = 2u, AR_DEBUG_CHECK_LINES = 4u, AR_DEBUG_TRACE = 8u };
 
 typedef struct ar_plan_s ar_plan_t;
@@ -180,7 +184,9 @@ typedef struct ar_plan_desc {
     int dtype;             /* AR_FLOAT32 or AR_BFLOAT16 */
     size_t count;          /* elements per rank; 0 is a valid no-op */
     int proto;             /* AR_PROTO_*; AUTO asks the tuner */
-    int nchannels;         /* 1 .. AR_MAX_CHANNELS; 0 asks the tuner */
+    int nchannels;         /* 1 .. AR_MAX_CHANNELS; 0 asks the tuner.  How many
+                              workgroups and waves it stands for depends on
+                              where a ring's links are: AR_PLAN_FIFO_ONLY */
     size_t chunk_bytes;    /* data bytes per ring step per (segment, channel);
                               0 asks the tuner / default */
     int fifo_depth;        /* FIFO slots per connection (2..16); 0 = default:
@@ -199,8 +205,9 @@ typedef struct ar_plan_desc {
     int algo;              /* AR_ALGO_* */
     int coll;              /* AR_COLL_* (0 = AllReduce) */
     int direct_unroll;     /* direct algorithm: 1 or 2 units per thread and
-                              iteration (times 2 for 2..4 ranks, times 4 for
-                              AllGather); 0 asks the tuner / default */
+                              iteration (up to times 2 for 2..4 ranks, times
+                              4 for AllGather; always 1 beyond eight ranks);
+                              0 asks the tuner / default */
 } ar_plan_desc;
 
 /* Plan flags.
@@ -237,9 +244,14 @@ typedef struct ar_plan_desc {
 enum { AR_PLAN_PROFILE = 1u, AR_PLAN_FIFO_ONLY = 2u, AR_PLAN_LL128_ORDERED = 4u };
 
 /* Resolved plan geometry (after the tuner and defaults).  The fields of
- * links in memory (waves, chunk, slots, FIFO and flag bytes, messages, wire
- * bytes) are filled for every ring plan, also for one whose links are in LDS,
- * which uses and allocates none of it. */
+ * links in memory (grid, block, waves, chunk, slots, FIFO and flag bytes,
+ * messages, wire bytes) are filled for every ring plan, also for one whose
+ * links are in LDS, which uses and allocates none of it: it launches the
+ * rings described at AR_PLAN_FIFO_ONLY, and moves compulsory bytes alone.
+ * Whether a ring is accepted goes by these fields wherever its links are
+ * (AR_ERR_OCCUPANCY, and AR_ERR_SCRATCH of ar_run_noalloc).  A direct plan
+ * launches grid workgroups of block threads too, but those of more than eight
+ * waves as two each, and one more for a partial unit at the end of the data. */
 typedef struct ar_plan_info {
     int nranks, dtype, proto, nchannels, nwaves, fifo_depth, placement;
     int grid;              /* workgroups = nchannels * nranks */

@@ -138,10 +138,21 @@ inline uint64_t ring_lds_workgroups(const ar_plan_info &g, uint64_t seg_b, uint6
 // written back at the end of the kernel while everything waits (8 ranks,
 // AllReduce, device time, non-temporal against sc1: 256 KiB fp32 3.0 and 2.2
 // us, 1 MiB bf16 4.2 and 3.3 us, 8 MiB fp32 24.8 and 21.9 us; AllGather of
-// 12 MiB 20.8 and 17.4 us; ReduceScatter of 64 MiB bf16 104.7 and 97.1 us;
-// the other way round only near 16 MiB in all, 6.0 and 6.2 us).  More: the
-// hint, which keeps them from driving each other and the inputs out (20 MiB
-// bf16 58.4 and 61.8 us, 32 MiB 92.8 and 97 us, 64 MiB fp32 186 and 196 us).
+// 12 MiB 20.8 and 17.4 us; ReduceScatter of 64 MiB bf16 104.7 and 97.1 us).
+// More: the hint, which keeps them from driving each other and the inputs out
+// (20 MiB bf16 58.4 and 61.8 us, 32 MiB 92.8 and 97 us, 64 MiB fp32 186 and
+// 196 us).
+//
+// What sc1 gains depends on what the cache still holds.  Its time over the
+// hint's, direct algorithm, fp32, by the outputs of all ranks: the same
+// buffers over and over / three sets in turn / buffers that the cache has lost:
+//   AllReduce, 8 ranks      4 MiB .94 / .91 / 1.00    12 MiB .77 / 1.17 / 1.22
+//                          24 MiB 1.08 / 1.12 / 1.10  48 MiB .93 / .92 / 1.04
+//   ReduceScatter, 8 ranks  2 MiB .94 / 1.11 / 1.09   64 MiB .97 / .95 / .96
+//   AllGather, 8 ranks     16 MiB .94 / .95 / 1.05    64 MiB .93 / .89 / 1.09
+//   AllGather, 5 ranks     30 MiB .76 / .74 / 1.49    80 MiB .66 / .69 / 1.14
+// It costs most where outputs start off the 128-byte lines (5 ranks' blocks)
+// and the cache has to fetch what a partial line lacks.
 inline bool outputs_fit_cache(const ar_plan_info &g)
 {
     const uint64_t rank = g.count * (g.dtype == AR_FLOAT32 ? 4 : 2) *

@@ -29,7 +29,14 @@ plan resolved them; when the fixed default is within 2 % the row defers to
 it.  The direct algorithm's columns take its fastest {workgroups per
 segment, waves, units per thread}, ties within 2 % going to fewer resolved
 workgroups.  The algorithm column picks the faster of the two (the direct
-algorithm on a tie: it moves fewer bytes).
+algorithm on a tie).
+
+Ring candidates run as default plans do, with their links in LDS, where
+channels times waves is all that matters: candidates that differ in protocol
+or chunk alone run the same kernel and tie.  The table in the library keeps
+the protocols and chunks that this rule selected while links were in memory,
+and direct columns set by hand (see its comment): emitting a table anew
+replaces both.
 """
 from __future__ import annotations
 
@@ -317,9 +324,11 @@ def emit_one(table, key, measured_as=None):
         "// ties within 2% broken by fewer channels, fewer wire bytes, smaller chunk).",
         "// AR_PROTO_AUTO ring columns defer to the fixed default (Simple, 16 channels):",
         "// there the default measured within 2% of the best ring choice (on the",
-        "// sweep, or when validated on fresh repeats).  The",
+        "// sweep, or when validated on fresh repeats).  With links in LDS, as the",
+        "// sweep runs them, protocol and chunk make no difference.  The direct columns",
+        "// are the fastest measured, ties within 2% going to fewer workgroups.  The",
         "// algorithm column picks the faster of the best ring and the best direct",
-        "// choice (direct on a tie, as it moves fewer bytes).",
+        "// choice (direct on a tie).",
         "//",
         "// columns: log2(size), ring proto, nchannels, chunk_bytes, nwaves, algorithm,",
         "//          direct parts, direct waves, direct unroll   [busBW GB/s: ring / direct]",
