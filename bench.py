@@ -51,7 +51,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 PROFILES = os.path.join(ROOT, "profiles")
 CSRC = os.path.join(ROOT, "paper_2603_11438_amd", "csrc")
-KERNEL_SRCS = ("ar_device.h", "ar_kernels.hip", "ring_lds.hip", "direct.hip")
+# the kernels, and what chooses among them (ar_internal.h: store policy, number of rings)
+KERNEL_SRCS = ("ar_device.h", "ar_internal.h", "ar_kernels.hip", "ring_lds.hip", "direct.hip")
 
 
 def kernel_source_hash() -> str:
@@ -72,9 +73,9 @@ def links(info: dict) -> str | None:
 def geometry_key(info: dict) -> str:
     """The launch geometry a counter summary was taken with."""
     if info["algo_name"] == "direct":
-        return f"direct parts={info['nchannels']} W={info['nwaves']}"
+        return f"direct parts={info['nchannels']} W={info['nwaves']} U={info['direct_unroll']}"
     if links(info) == "lds":
-        return f"ring links=lds C={info['nchannels']}"
+        return f"ring links=lds C={info['nchannels']} W={info['nwaves']}"
     return (f"ring proto={info['proto_name']} C={info['nchannels']} W={info['nwaves']} "
             f"chunk_elems={info['chunk_elems']} depth={info['fifo_depth']} links=fifo")
 
