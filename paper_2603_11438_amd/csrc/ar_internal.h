@@ -151,8 +151,10 @@ inline uint64_t ring_lds_workgroups(const ar_plan_info &g, uint64_t seg_b, uint6
 //   ReduceScatter, 8 ranks  2 MiB .94 / 1.11 / 1.09   64 MiB .97 / .95 / .96
 //   AllGather, 8 ranks     16 MiB .94 / .95 / 1.05    64 MiB .93 / .89 / 1.09
 //   AllGather, 5 ranks     30 MiB .76 / .74 / 1.49    80 MiB .66 / .69 / 1.14
-// It costs most where outputs start off the 128-byte lines (5 ranks' blocks)
-// and the cache has to fetch what a partial line lacks.
+// It costs most where outputs start off the memory side's lines (5 ranks'
+// blocks) and the cache has to fetch what a partial line lacks; the direct
+// algorithm's iterations therefore start on lines (direct.hip; without that
+// the figures above).
 inline bool outputs_fit_cache(const ar_plan_info &g)
 {
     const uint64_t rank = g.count * (g.dtype == AR_FLOAT32 ? 4 : 2) *

@@ -551,7 +551,8 @@ static void fit_direct_to_ranks(const ar_tune_ctx &c, ar_tune_out *out)
         // uneven (their scaled grids end a little above 256, see below).
         // About 1024 workgroups even that out, of four waves and one unit per
         // thread, or, for AllReduce beyond 64 MiB, of one wave and two units
-        // (row's geometry / four waves / one wave, AllReduce: 6 ranks, fp32,
+        // (before iterations started on lines, which takes 2 to 15 % off each:
+        // row's geometry / four waves / one wave, AllReduce: 6 ranks, fp32,
         // 48 MiB 152 / 112 / 111 us, 128 MiB 448 / 333 / 321; 7 ranks, fp32,
         // 12 MiB 47 / 35 / 36, 128 MiB 559 / 417 / 392, bf16, 128 MiB 393 /
         // 418 / 388; ReduceScatter bf16, 7 ranks, 96 MiB 200 / 151).
