@@ -545,12 +545,14 @@ static void fit_direct_to_ranks(const ar_tune_ctx &c, ar_tune_out *out)
     const uint64_t e = c.dtype == AR_FLOAT32 ? 4 : 2, n = (uint64_t)c.nranks;
     const uint64_t units = ceil_div(ceil_div(c.msg_bytes / e, n), 16 / e);  // 16-byte units of a segment
     const bool large = c.msg_bytes > (8u << 20);  // a thread has several iterations
-    if (large && c.coll != AR_COLL_ALLGATHER && n > 4 && n % 4 != 0) {
-        // A sum over ranks that are no multiple of four: a segment's workgroups fall on
-        // all XCDs in turn, and the rows' few long-lived workgroups come out
-        // uneven (their scaled grids end a little above 256, see below).
-        // About 1024 workgroups even that out, of four waves and one unit per
-        // thread, or, for AllReduce beyond 64 MiB, of one wave and two units
+    const bool sum = c.coll == AR_COLL_ALLREDUCE || c.coll == AR_COLL_REDUCESCATTER;
+    if (large && sum && n > 4 && n % 4 != 0) {
+        // A sum over ranks that are no multiple of four: a segment's
+        // workgroups fall on all XCDs in turn, and the rows' few long-lived
+        // workgroups come out uneven (their scaled grids end a little above
+        // 256, see below).  About 1024 workgroups even that out, of four waves
+        // and one unit per thread, or, for AllReduce beyond 64 MiB, of one
+        // wave and two units
         // (before iterations started on lines, which takes 2 to 15 % off each:
         // row's geometry / four waves / one wave, AllReduce: 6 ranks, fp32,
         // 48 MiB 152 / 112 / 111 us, 128 MiB 448 / 333 / 321; 7 ranks, fp32,

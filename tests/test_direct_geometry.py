@@ -78,3 +78,12 @@ def test_parts_no_launch_can_hold(parts, n, count, waves):
     assert info["nchannels"] == (parts if parts <= room else min(units, room))
     assert info["grid"] == info["nchannels"] * n > 0
     assert (info["grid"] * split + 1) * threads < 1 << 32
+
+
+def test_no_opinion_on_other_collectives():
+    """A collective that is not tabulated gets the default, at every rank count."""
+    ar.lib()
+    for n in (2, 5, 7, 8, 16):
+        got = ar.ar_tune(64 << 20, n, "f32", coll=9)
+        assert (got["direct_parts"], got["direct_nwaves"], got["direct_unroll"]) == (0, 0, 0)
+        assert (got["proto_name"], got["nchannels"]) == ("simple", 16)
